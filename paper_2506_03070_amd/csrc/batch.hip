@@ -243,32 +243,54 @@ __global__ __launch_bounds__(kPanelThreads) void batch_qr_first_kernel(const Bat
   const BatchItem &it = items[blockIdx.x];
   const int rows = it.d, cols = it.n + 1;
   const int nb = cols < NB ? cols : NB;
-  double P[S][NB];
-  load_block<S, NB>(it.Y, rows, 0, rows, 0, nb, P);
-  factor_panel<S, NB>(P, sh, nb, rows, 0, 0, it.tau, it.T0);
-  store_block<S, NB>(it.Y, rows, 0, rows, 0, nb, P);
+  double P[S][NB], V[S][NB];
+  load_columns<S, NB, kPanelThreads, 0>(it.Y, rows, rows, nb, 0, P);
+#pragma unroll
+  for (int s = 0; s < S; ++s)
+#pragma unroll
+    for (int i = 0; i < NB; ++i) V[s][i] = 0.0;
+  gram_prepare<S, NB, kPanelThreads>(P, sh, 0);
+  __syncthreads();
+  factor_update<S, NB, kPanelThreads>(
+      P, V, 0.0, sh, nb, rows, 0, 0, it.tau, true, true, [](int, int, double) {}, [&](int e, double v) { it.T0[e] = v; });
+  store_columns<S, NB, kPanelThreads, 0>(it.Y, rows, rows, nb, 0, P);
 }
 
+// Step `step`: panel k0 = step NB is applied to the trailing columns, one
+// block of NB a workgroup (rows from k0); block 0 becomes the next panel.
 template <int S, int NB>
 __global__ __launch_bounds__(kPanelThreads) void batch_qr_step_kernel(const BatchItem *__restrict__ items, int step) {
   __shared__ PanelShared<NB> sh;
   const BatchItem &it = items[blockIdx.y];
   const int rows = it.d, cols = it.n + 1;
   const int k0 = step * NB;
-  const int nb = min(NB, cols - k0);
-  if (nb <= 0 || k0 + nb >= cols) return;  // no trailing columns at this step
-  const int trailing = cols - (k0 + nb);
-  if (static_cast<int>(blockIdx.x) * NB >= trailing) return;
-  const int c0 = k0 + nb + static_cast<int>(blockIdx.x) * NB;
+  if (k0 + NB >= cols) return;  // no trailing columns at this step
+  const int c0 = k0 + NB + static_cast<int>(blockIdx.x) * NB;
+  if (c0 >= cols) return;
   const int ncb = min(NB, cols - c0);
   const int dr = rows - k0;
   const double *Tcur = (step & 1) ? it.T1 : it.T0;
   double *Tnext = (step & 1) ? it.T0 : it.T1;
-  double C[S][NB];
-  load_block<S, NB>(it.Y, rows, k0, dr, c0, ncb, C);
-  apply_panel_qt<S, NB>(it.Y, rows, dr, k0, nb, Tcur, C, ncb, sh);
-  if (blockIdx.x == 0) factor_panel<S, NB>(C, sh, ncb, rows - c0, c0 - k0, c0, it.tau, Tnext);
-  store_block<S, NB>(it.Y, rows, k0, dr, c0, ncb, C);
+  double *base = it.Y + k0 + static_cast<int64_t>(c0) * rows;
+  const double tel = Tcur[(threadIdx.x & (kWave - 1)) % (NB * NB)];  // in flight with the loads below
+  double C[S][NB], V[S][NB];
+  load_columns<S, NB, kPanelThreads, 0>(base, rows, dr, ncb, 0, C);
+  load_columns<S, NB, kPanelThreads, 0>(it.Y + k0 + static_cast<int64_t>(k0) * rows, rows, dr, NB, 0, V);
+  if (blockIdx.x == 0) gram_prepare<S, NB, kPanelThreads>(C, sh, NB);
+  unit_lower<S, NB, kPanelThreads>(V, 0);
+  if (blockIdx.x == 0) {
+    __syncthreads();
+    factor_update<S, NB, kPanelThreads>(
+        C, V, tel, sh, ncb, dr, NB, c0, it.tau, true, true,
+        [&](int r, int x, double v) {
+          if (x < ncb) base[r + static_cast<int64_t>(x) * rows] = v;
+        },
+        [&](int e, double v) { Tnext[e] = v; });
+    store_columns<S, NB, kPanelThreads, 0>(base, rows, dr, ncb, NB, C);
+  } else {
+    apply_wy<S, NB, kPanelThreads>(V, C, tel, sh);
+    store_columns<S, NB, kPanelThreads, 0>(base, rows, dr, ncb, 0, C);
+  }
 }
 
 __global__ __launch_bounds__(256) void batch_rank_kernel(BatchItem *__restrict__ items) {

@@ -11,14 +11,20 @@
 //     workgroup-wide sums, W2 = T^T W, C -= V W2), as soon as panel k's owner
 //     has published it: reflectors and T written through to the coherence
 //     point shared by the XCDs, then a flag;
-//   * it then factors its own panel, one workgroup reduction per column for
-//     the norm below the diagonal and one batched reduction that gives both
-//     v_j^T C (the update of the panel columns to its right) and V_{<j}^T v_j
-//     (the next column of T), and publishes it.
+//   * it then factors its own panel from its Gram matrix, summed before the
+//     last update arrives (factor_update in qr_dev.h), and publishes it.
 // The trailing matrix never goes back to memory between panels and no launch
 // boundary separates them: a panel's critical path is one block apply and one
 // panel factorisation.  A workgroup only waits for workgroups that started
 // before it, so the chain completes whatever number of them is resident.
+//
+// What bounds it: the dependent chain from panel to panel (not the flops: 4%
+// of the FP64 peak at 4000 x 1001).  Per 4-column panel at 4000 rows 8.5 us:
+// flag seen 0.8, reflectors in 1.3, V^T C 1.5, W2 0.4, the panel's 4
+// reflectors 1.6, update and new rows 0.8, rows out and acknowledged 2.4 (16.0
+// us with one workgroup reduction per column and selects on every row: apply
+// 6.7, factor 6.5).  4000 x 1001: 3.95 -> 2.12 ms, 1026 x 257: 0.75 -> 0.40,
+// 400 x 101: 0.23 -> 0.12, 8000 x 1001: 6.65 -> 5.0.
 // Sketches taller than 4096 rows and wider than 192 columns take the
 // two-level form below: 64-column panels factored by the chained form, the
 // trailing matrix updated on the FP64 matrix cores.
@@ -34,69 +40,15 @@ namespace {
 
 using namespace qr_dev;
 
-// Chained QR: C <- (I - V T^T V^T) C for a block held at fixed rows (thread t
-// holds rows t + TH s of the whole column block), with panel k's reflectors
-// (columns k0 .. k0+nbp-1 of Y, rows from k0, unit diagonal implicit) and T
-// read through the coherence point, since another workgroup wrote them
-// during this launch.  Rows above the panel have V = 0 and are unchanged.
-template <int S, int NB, int TH>
-__device__ __forceinline__ void chain_apply_panel(const double *__restrict__ Y, int64_t ldy, int d, int k0, int nbp,
-                                                  const double *__restrict__ T, double (&C)[S][NB], int ncb,
-                                                  PanelShared<NB, TH> &sh) {
-  const int t = threadIdx.x;
-  const int lane = t & (kWave - 1), wave = t / kWave;
-  const double tload = t < NB * NB ? load_coherent(T + t) : 0.0;
-  double V[S][NB];
-#pragma unroll
-  for (int s = 0; s < S; ++s) {
-    const int r = t + TH * s;
-    const int lr = r - k0;
-    const int rr = min(max(r, k0), d - 1);  // in-range address; masked below
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-      const double y = load_coherent(Y + static_cast<int64_t>(k0 + min(i, nbp - 1)) * ldy + rr);
-      V[s][i] = (i < nbp && lr >= 0 && r < d) ? vval(lr, i, y) : 0.0;
-    }
-  }
-  if (t < NB * NB) sh.Tl[t] = tload;
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < NB; ++i)
-#pragma unroll
-    for (int c = 0; c < NB; ++c) {
-      double acc = 0.0;
-#pragma unroll
-      for (int s = 0; s < S; ++s) acc += V[s][i] * C[s][c];
-      acc = wave_sum_u(acc);
-      if (lane == 0) sh.red[wave][i * NB + c] = acc;
-    }
-  __syncthreads();
-  if (t < NB * NB) {
-    const int i = t / NB, c = t % NB;
-    double s_ = 0.0;
-    for (int l = 0; l <= i && l < nbp; ++l) {
-      double wlc = 0.0;
-      for (int w = 0; w < (TH / kWave); ++w) wlc += sh.red[w][l * NB + c];
-      s_ += sh.Tl[l + i * NB] * wlc;
-    }
-    sh.W2[i][c] = (i < nbp && c < ncb) ? s_ : 0.0;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int s = 0; s < S; ++s)
-#pragma unroll
-    for (int c = 0; c < NB; ++c) {
-      double acc = 0.0;
-#pragma unroll
-      for (int i = 0; i < NB; ++i) acc += V[s][i] * sh.W2[i][c];
-      C[s][c] -= acc;
-    }
-}
-
 // A wait of the chain gives up after this many polls (a producer that never
 // ran, which the start-ordered tickets rule out); the block is then NaN, which
 // the rank test that follows every solve's QR reports as a non-finite R.
 constexpr int kQrSpinLimit = 1 << 20;
+
+// A block takes its last kWarm panels through the factorisation's code (which
+// it needs once in its life), so that it is in the instruction cache when the
+// last one arrives.
+constexpr int kWarm = 3;
 
 // One launch of ceil(cols / NB) workgroups; w: the ticket word and one flag
 // per panel, zero on entry; Tall: NB x NB per panel.
@@ -105,7 +57,6 @@ __global__ __launch_bounds__(TH) void qr_chain_kernel(double *__restrict__ Y, in
                                                       double *__restrict__ Tall, double *__restrict__ tau,
                                                       int *__restrict__ w) {
   __shared__ PanelShared<NB, TH> sh;
-  __shared__ double Tsh[NB * NB];
   __shared__ int jsh, failed;
   const int t = threadIdx.x;
   if (t == 0) {
@@ -113,14 +64,19 @@ __global__ __launch_bounds__(TH) void qr_chain_kernel(double *__restrict__ Y, in
     failed = 0;
   }
   __syncthreads();
-  const int j = jsh;
+  const int j = __builtin_amdgcn_readfirstlane(jsh);
   int *flags = w + 1;
   const int c0 = j * NB;
   const int ncb = min(NB, cols - c0);
+  double *base = Y + static_cast<int64_t>(c0) * ldy;
   double C[S][NB];
-  load_block<S, NB, TH>(Y, ldy, 0, d, c0, ncb, C);
-  for (int k = 0; k < j; ++k) {
-    if (t == 0) {
+  load_columns<S, NB, TH, 0>(base, ldy, d, ncb, 0, C);
+  const auto store_t = [&](int e, double v) { store_coherent(Tall + j * NB * NB + e, v); };
+  if (j <= kWarm) gram_prepare<S, NB, TH>(C, sh, min(j, 1) * NB);
+  bool expired = false;
+  // the first block (j = 0) makes one round without reflectors, k = -1
+  for (int k = min(j, 1) - 1; k < j; ++k) {
+    if (t == 0 && k >= 0) {
       int spins = 0;
       while (__hip_atomic_load(flags + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < 1) {
         __builtin_amdgcn_s_sleep(1);
@@ -131,29 +87,31 @@ __global__ __launch_bounds__(TH) void qr_chain_kernel(double *__restrict__ Y, in
       }
     }
     __syncthreads();
-    if (failed) break;  // uniform
-    chain_apply_panel<S, NB, TH>(Y, ldy, d, k * NB, min(NB, cols - k * NB), Tall + k * NB * NB, C, ncb, sh);
+    expired = __builtin_amdgcn_readfirstlane(failed) != 0;
+    if (expired) break;
+    // Panel k's reflectors (a full panel: k < j) at the rows this block's
+    // threads hold, and T (element e in lane e of every wave), through the
+    // coherence point: another workgroup wrote them during this launch.
+    const int k0 = k * NB;
+    const double tel = k < 0 ? 0.0 : load_coherent(Tall + k * NB * NB + (t & (kWave - 1)) % (NB * NB));
+    double V[S][NB];
+    load_columns<S, NB, TH, kCoherent>(Y + static_cast<int64_t>(max(k0, 0)) * ldy, ldy, k < 0 ? 0 : d, NB, k0, V);
+    unit_lower<S, NB, TH>(V, k0);
+    const auto put_r = [&](int r, int x, double v) {
+      if (x < ncb) base[k0 + r + static_cast<int64_t>(x) * ldy] = v;
+    };
+    const bool last = k == j - 1, warm = k >= j - kWarm;
+    factor_update<S, NB, TH>(C, V, tel, sh, ncb, d, k0 + NB, c0, tau, warm, last, put_r, store_t);
+    // G while the next panel is still on its way
+    if (warm && !last) gram_prepare<S, NB, TH>(C, sh, k0 + 2 * NB);
   }
-  if (failed) {
+  if (expired) {
 #pragma unroll
     for (int s = 0; s < S; ++s)
 #pragma unroll
       for (int c = 0; c < NB; ++c) C[s][c] = __builtin_nan("");
-  } else {
-    factor_panel<S, NB>(C, sh, ncb, d - c0, c0, c0, tau, Tsh);
-    __syncthreads();
-    if (t < NB * NB) store_coherent(Tall + j * NB * NB + t, Tsh[t]);
   }
-  double *__restrict__ base = Y + static_cast<int64_t>(c0) * ldy;
-#pragma unroll
-  for (int s = 0; s < S; ++s) {
-    const int r = t + TH * s;
-    if (r < d) {
-#pragma unroll
-      for (int c = 0; c < NB; ++c)
-        if (c < ncb) store_coherent(base + static_cast<int64_t>(c) * ldy + r, C[s][c]);
-    }
-  }
+  store_columns<S, NB, TH, kCoherent>(base, ldy, d, ncb, c0, C);
   publish_flag(flags + j, 1);
 }
 
