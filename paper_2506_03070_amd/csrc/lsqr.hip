@@ -1,6 +1,6 @@
 // Preconditioned LSQR (Alg. 2) on A M, M = R^-1, for gfx950.
 //
-// One iteration is five kernels on one stream, with no host round trip:
+// One iteration is four kernels on one stream, with no host round trip:
 //   1. pass   : one sweep over A computing, for every row i,
 //                 u_i <- c_ap (A p)_i + c_u u_i        (p = M v_t)
 //               and accumulating q = A^T u and ||u||^2 from the same
@@ -12,9 +12,9 @@
 //   2. q_slices: the partials summed in fixed-order slices;
 //   3. mtq    : v_hat = M^T q / beta - beta v and the partials of ||v_hat||^2
 //               (M = R^-1 formed once per solve, Sec. 3.2);
-//   4. mv     : alpha, v = v_hat / alpha, p = M v;
-//   5. update : plane rotation, x += (phi/rho) w, w = p - (theta/rho) w, the
-//               stopping test and the coefficients of the next pass.
+//   4. mv     : alpha, v = v_hat / alpha, p = M v, the plane rotation,
+//               x += (phi/rho) w, w = p - (theta/rho) w, the stopping test and
+//               the coefficients of the next pass.
 // All scalars stay in device memory.  Kernels early-exit once the device
 // `done` flag is set, so the host enqueues iterations in batches of eight
 // (captured once into a hipGraph and replayed) and reads the flag once per
@@ -373,25 +373,90 @@ __global__ __launch_bounds__(256) void inverse_transpose_kernel(const double *__
   trsv_transpose_tile(M, n, n, static_cast<int>(blockIdx.x), static_cast<int>(blockIdx.y), Mt, tile);
 }
 
+// The kernels between two passes move little (n^2 / 2 entries of M twice, G n
+// of partials once) and are bound by load latency: each issues the loads that
+// its inputs do not decide before it waits for the ones that do, and keeps at
+// least eight in flight.  At n = 500 (G = 512) the three of an iteration take
+// 18 us (4.7 + 5 + 8, of which 4 is what an empty launch takes); with loads
+// waited for one by one and the update a launch of its own, 33.
+
 // q = sum over the pass partials, in two fixed-order levels: this kernel sums
 // slice s (kQSlice consecutive partials) for 64 columns; the GEMV kernels sum
 // the slices.
 constexpr int kQSlice = 64;
-__global__ __launch_bounds__(256) void q_slices_kernel(const double *__restrict__ qpart, int G, int n,
-                                                       double *__restrict__ qs) {
-  __shared__ double red[4][64];
+constexpr int kMaxQSlices = 16;
+__global__ __launch_bounds__(1024) void q_slices_kernel(const double *__restrict__ qpart, int G, int n,
+                                                        double *__restrict__ qs, const LsqrState *__restrict__ st) {
+  constexpr int kSub = 1024 / 64, kPer = kQSlice / kSub;
+  __shared__ double red[kSub][64];
+  if (st->done) return;
   const int t = threadIdx.x;
   const int cl = t % 64, sub = t / 64;
   const int c = blockIdx.x * 64 + cl;
   const int g0 = blockIdx.y * kQSlice;
-  const int g1 = min(G, g0 + kQSlice);
+  double v[kPer];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int g = g0 + sub + kSub * k;
+    v[k] = qpart[static_cast<int64_t>(min(g, G - 1)) * n + min(c, n - 1)];
+  }
   double s = 0.0;
-  if (c < n)
-    for (int g = g0 + sub; g < g1; g += 4) s += qpart[static_cast<int64_t>(g) * n + c];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) s += g0 + sub + kSub * k < G ? v[k] : 0.0;
   red[sub][cl] = s;
   __syncthreads();
-  if (sub == 0 && c < n) qs[static_cast<int64_t>(blockIdx.y) * n + c] = red[0][cl] + red[1][cl] + red[2][cl] + red[3][cl];
+  if (sub == 0 && c < n) {
+    s = 0.0;
+#pragma unroll
+    for (int k = 0; k < kSub; ++k) s += red[k][cl];
+    qs[static_cast<int64_t>(blockIdx.y) * n + c] = s;
+  }
 }
+
+// q[c], c < n, from the slices into LDS (1024 threads, no barrier).
+__device__ __forceinline__ void sum_slices(const double *__restrict__ qs, int nslices, int n, double *q) {
+  for (int c = threadIdx.x; c < n; c += 1024) {
+    double v[kMaxQSlices];
+#pragma unroll
+    for (int k = 0; k < kMaxQSlices; ++k)
+      if (k < nslices) v[k] = qs[static_cast<int64_t>(k) * n + c];
+    double a = 0.0;
+#pragma unroll
+    for (int k = 0; k < kMaxQSlices; ++k)
+      if (k < nslices) a += v[k];
+    q[c] = a;
+  }
+}
+
+// Dot product of col[lo .. hi) (global) with vec[lo .. hi) (LDS) by one wave.
+// The first kAhead 64-entry steps of col are loaded by the constructor, before
+// vec is known; the rest kAhead at a time.
+struct ColumnDot {
+  static constexpr int kAhead = 8;
+  const double *col;
+  int k0, hi;
+  double c[kAhead];
+  __device__ __forceinline__ ColumnDot(const double *col_, int lo, int hi_) : col(col_), hi(hi_) {
+    k0 = lo + (static_cast<int>(threadIdx.x) & (kWave - 1));
+    load();
+  }
+  __device__ __forceinline__ void load() {
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) c[u] = k0 + kWave * u < hi ? col[k0 + kWave * u] : 0.0;
+  }
+  __device__ __forceinline__ double with(const double *vec) {
+    double acc = 0.0;
+    for (;;) {
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u)
+        if (k0 + kWave * u < hi) acc += c[u] * vec[k0 + kWave * u];
+      k0 += kWave * kAhead;
+      if (__builtin_amdgcn_readfirstlane(k0) >= hi) break;
+      load();
+    }
+    return wave_sum_u(acc);
+  }
+};
 
 // beta = ||u_hat|| from the pass partials (fixed order, every workgroup the same).
 __device__ __forceinline__ double beta_from_partials(const double *__restrict__ nrmpart, int G, double *scr) {
@@ -411,23 +476,17 @@ __global__ __launch_bounds__(1024) void lsqr_mtq_kernel(const double *__restrict
   __shared__ double q[kMaxN];
   __shared__ double wsum[16];
   if (st->done) return;
-  const double beta = beta_from_partials(nrmpart, G, scr);
   const int t = threadIdx.x;
-  for (int c = t; c < n; c += 1024) {
-    double a = 0.0;
-    for (int s = 0; s < nslices; ++s) a += qs[static_cast<int64_t>(s) * n + c];
-    q[c] = a;
-  }
-  __syncthreads();
-  const int lane = t & (kWave - 1), wave = t / kWave;
+  const int lane = t & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(t / kWave);
   const int j = blockIdx.x * 16 + wave;
+  ColumnDot dot(M + static_cast<int64_t>(min(j, n - 1)) * n, 0, min(j, n - 1) + 1);
+  const double vj = v[min(j, n - 1)];
+  sum_slices(qs, nslices, n, q);
+  const double beta = beta_from_partials(nrmpart, G, scr);  // its barriers follow the writes of q
   double sq = 0.0;
   if (j < n) {
-    const double *__restrict__ col = M + static_cast<int64_t>(j) * n;
-    double acc = 0.0;
-    for (int k = lane; k <= j; k += kWave) acc += col[k] * q[k];
-    acc = wave_sum_u(acc);
-    const double vhj = beta > 0.0 ? acc / beta - (st->init ? 0.0 : beta * v[j]) : 0.0;
+    const double acc = dot.with(q);
+    const double vhj = beta > 0.0 ? acc / beta - (st->init ? 0.0 : beta * vj) : 0.0;
     if (lane == 0) vh[j] = vhj;
     sq = vhj * vhj;
   }
@@ -440,58 +499,95 @@ __global__ __launch_bounds__(1024) void lsqr_mtq_kernel(const double *__restrict
   }
 }
 
-// alpha = ||v_hat||, v = v_hat / alpha, p = M v; one wave per entry r (row r
-// of M = column r of M^T, rows r..n-1).  Workgroup 0 records beta, alpha.
+// alpha = ||v_hat||, v = v_hat / alpha, p = M v, then the initialisation (w =
+// p) or the plane rotation of Alg. 2 with x += (phi/rho) w, w = p -
+// (theta/rho) w; one wave per entry r (row r of M = column r of M^T, rows
+// r..n-1).  Every workgroup takes the same scalars from the same state and
+// partials; the last one to finish (the ticket, zero before and after) writes
+// the new state, once all have read the old one.
 __global__ __launch_bounds__(1024) void lsqr_mv_kernel(const double *__restrict__ Mt, int n,
                                                        const double *__restrict__ vh, const double *__restrict__ vpart,
                                                        int nvpart, const double *__restrict__ nrmpart, int G,
                                                        double *__restrict__ v, double *__restrict__ p,
-                                                       float *__restrict__ p32, LsqrState *st) {
-  __shared__ double scr[16];
+                                                       float *__restrict__ p32, double *__restrict__ w,
+                                                       double *__restrict__ x, unsigned int *ticket, LsqrState *st) {
+  __shared__ double scr[16], scr2[16];
   __shared__ double vs[kMaxN];
   if (st->done) return;
-  const double beta = beta_from_partials(nrmpart, G, scr);
   const int t = threadIdx.x;
+  const int lane = t & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(t / kWave);
+  const int rr = blockIdx.x * 16 + wave;
+  const int rc = min(rr, n - 1);
+  ColumnDot dot(Mt + static_cast<int64_t>(rc) * n, rc, n);
+  const double wr = w[rc], xr = x[rc];
+  for (int c = t; c < n; c += 1024) vs[c] = vh[c];
+  const LsqrState s0 = *st;
   double asq = 0.0;
   for (int k = t; k < nvpart; k += 1024) asq += vpart[k];
-  const double alpha = beta > 0.0 ? sqrt(wg_sum(asq, scr)) : 0.0;
+  const double beta = beta_from_partials(nrmpart, G, scr);  // its barriers follow the writes of vs
+  const double anorm = sqrt(wg_sum(asq, scr2));
+  const double alpha = beta > 0.0 ? anorm : 0.0;
   const bool proceed = beta > 0.0 && alpha > 0.0;
-  if (!proceed) {
-    if (blockIdx.x == 0 && t == 0) {
-      st->beta_new = beta;
-      st->alpha_new = alpha;
-      st->proceed = 0;
+  const bool init = s0.init != 0;
+  const double ia = proceed ? 1.0 / alpha : 0.0;
+  // plane rotation with beta_{t+1}, alpha_{t+1}
+  const double rho = sqrt(s0.rhobar * s0.rhobar + beta * beta);
+  const double cs = s0.rhobar / rho, sn = beta / rho;
+  const double theta = sn * alpha;
+  const double phi = cs * s0.phibar;
+  const double fx = phi / rho, fw = theta / rho;
+  if (rr < n) {
+    const double pr = proceed ? ia * dot.with(vs) : 0.0;
+    if (lane == 0) {
+      if (proceed) {
+        p[rr] = pr;
+        if (p32) p32[rr] = static_cast<float>(pr);
+        v[rr] = vs[rr] * ia;
+        w[rr] = init ? pr : pr - fw * wr;
+      }
+      if (!init) x[rr] = xr + fx * wr;
     }
+  }
+  // this workgroup has read all it takes from the state
+  __syncthreads();
+  if (t != 0) return;
+  if (atomicAdd(ticket, 1u) != gridDim.x - 1) return;
+  *ticket = 0;
+  st->beta_new = beta;
+  st->alpha_new = alpha;
+  st->proceed = proceed ? 1 : 0;
+  st->alpha = alpha;
+  st->beta = beta;
+  st->c_ap = 1.0;
+  st->c_u = beta > 0.0 ? -alpha / beta : 0.0;
+  st->steps = s0.steps + 1;
+  if (init) {
+    // beta_1 u_1 = b - A x0, alpha_1 v_1 = M^T A^T u_1, w_1 = M v_1
+    st->init = 0;
+    st->phibar = beta;
+    st->rhobar = alpha;
+    st->resid_est = beta;
+    st->normar_est = alpha * beta;
+    st->normref = s0.rel ? beta : s0.normb;
+    st->normar0 = alpha * beta;
+    st->converged = proceed ? 0 : 1;
+    st->done = (!proceed || s0.maxiter <= s0.total_iters) ? 1 : 0;
     return;
   }
-  const double ia = 1.0 / alpha;
-  for (int c = t; c < n; c += 1024) vs[c] = vh[c] * ia;
-  __syncthreads();
-  const int lane = t & (kWave - 1), wave = t / kWave;
-  const int rr = blockIdx.x * 16 + wave;
-  if (rr < n) {
-    const double *__restrict__ col = Mt + static_cast<int64_t>(rr) * n;
-    double acc = 0.0;
-    for (int k = rr + lane; k < n; k += kWave) acc += col[k] * vs[k];
-    acc = wave_sum_u(acc);
-    if (lane == 0) {
-      p[rr] = acc;
-      if (p32) p32[rr] = static_cast<float>(acc);
-      v[rr] = vs[rr];
-    }
-  }
-  if (blockIdx.x == 0 && t == 0) {
-    st->beta_new = beta;
-    st->alpha_new = alpha;
-    st->proceed = 1;
-  }
-}
-
-// Plane rotation, x and w updates, stopping test (one workgroup).
-__global__ __launch_bounds__(kTrsvThreads) void lsqr_update_kernel(const double *p, double *__restrict__ w,
-                                                                   double *__restrict__ x, int n, LsqrState *st) {
-  if (st->done) return;
-  upper_epilogue(n, p, w, x, st, nullptr);
+  const double phibar = sn * s0.phibar;
+  const double normar = phibar * alpha * fabs(cs);
+  st->iter = s0.iter + 1;
+  st->total_iters = s0.total_iters + 1;
+  st->rhobar = -cs * alpha;
+  st->phibar = phibar;
+  st->resid_est = phibar;
+  st->normar_est = normar;
+  // Inner solves of the refinement form (rel) also stop once the normal-
+  // equation residual of their own problem has dropped by kInnerReduction.
+  const bool conv = !proceed || alpha * fabs(cs) <= s0.tol || phibar <= s0.tol * s0.normref ||
+                    (s0.rel && normar <= kInnerReduction * s0.normar0);
+  st->converged = conv ? 1 : 0;
+  st->done = (conv || s0.total_iters + 1 >= s0.maxiter) ? 1 : 0;
 }
 
 // Fresh state for an LSQR run; clears the chain flags of the two solves.
@@ -535,13 +631,15 @@ __global__ __launch_bounds__(1024) void norm_kernel(const double *__restrict__ b
     last = atomicAdd(ticket, 1u) == gridDim.x - 1;
   }
   __syncthreads();
-  if (last && threadIdx.x == 0) {
+  if (last) {  // one partial a thread (gridDim.x <= 1024)
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    double tot = 0.0;
-    for (unsigned g = 0; g < gridDim.x; ++g)
-      tot += __hip_atomic_load(&partial[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    st->normb = sqrt(tot);
-    *ticket = 0;
+    const unsigned g = threadIdx.x;
+    const double tot = wg_sum(
+        g < gridDim.x ? __hip_atomic_load(&partial[g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0, scr);
+    if (threadIdx.x == 0) {
+      st->normb = sqrt(tot);
+      *ticket = 0;
+    }
   }
 }
 
@@ -971,20 +1069,14 @@ __global__ __launch_bounds__(1024) void hbm_mtq_kernel(const double *__restrict_
   __shared__ double wsum[16];
   if (st->done) return;
   const int t = threadIdx.x;
-  for (int c = t; c < n; c += 1024) {
-    double a = 0.0;
-    for (int k = 0; k < nslices; ++k) a += qs[static_cast<int64_t>(k) * n + c];
-    q[c] = a;
-  }
-  __syncthreads();
-  const int lane = t & (kWave - 1), wave = t / kWave;
+  const int lane = t & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(t / kWave);
   const int j = blockIdx.x * 16 + wave;
+  ColumnDot dot(M + static_cast<int64_t>(min(j, n - 1)) * n, 0, min(j, n - 1) + 1);
+  sum_slices(qs, nslices, n, q);
+  __syncthreads();
   double sq = 0.0;
   if (j < n) {
-    const double *__restrict__ col = M + static_cast<int64_t>(j) * n;
-    double acc = 0.0;
-    for (int k = lane; k <= j; k += kWave) acc += col[k] * q[k];
-    acc = wave_sum_u(acc);
+    const double acc = dot.with(q);
     if (lane == 0) sv[j] = acc;
     sq = acc * acc;
   }
@@ -1015,6 +1107,11 @@ __global__ __launch_bounds__(1024) void hbm_step_kernel(const double *__restrict
   __shared__ double scr[16];
   __shared__ double ss[kMaxN];
   if (st->done) return;
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int rr = blockIdx.x * 16 + wave;
+  const int rc = min(rr, n - 1);
+  ColumnDot dot(Mt + static_cast<int64_t>(rc) * n, rc, n);
+  for (int c = threadIdx.x; c < n; c += 1024) ss[c] = sv[c];
   const int t = st->iter - 1;  // updates made: hbm_mtq_kernel advanced the counter for this step
   const double rn = beta_from_partials(nrmpart, G, scr);
   double a = 0.0;
@@ -1031,15 +1128,8 @@ __global__ __launch_bounds__(1024) void hbm_step_kernel(const double *__restrict
     }
     return;
   }
-  for (int c = threadIdx.x; c < n; c += 1024) ss[c] = sv[c];
-  __syncthreads();
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int rr = blockIdx.x * 16 + wave;
   if (rr < n) {
-    const double *__restrict__ col = Mt + static_cast<int64_t>(rr) * n;
-    double acc = 0.0;
-    for (int k = rr + lane; k < n; k += kWave) acc += col[k] * ss[k];
-    acc = wave_sum_u(acc);
+    const double acc = dot.with(ss);  // the norms' barriers follow the writes of ss
     if (lane == 0) {
       const double dl = alpha * acc + beta * delta[rr];
       delta[rr] = dl;
@@ -1060,15 +1150,14 @@ __global__ __launch_bounds__(1024) void sstep_mv_kernel(const double *__restrict
                                                         const double *__restrict__ in, double *__restrict__ out,
                                                         double *__restrict__ xacc) {
   __shared__ double v[kMaxN];
+  const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int r = blockIdx.x * 16 + wave;
+  const int rc = min(r, n - 1);
+  ColumnDot dot(Mt + static_cast<int64_t>(rc) * n, rc, n);
   for (int c = threadIdx.x; c < n; c += 1024) v[c] = in[c];
   __syncthreads();
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int r = blockIdx.x * 16 + wave;
   if (r >= n) return;
-  const double *__restrict__ col = Mt + static_cast<int64_t>(r) * n;
-  double acc = 0.0;
-  for (int k = r + lane; k < n; k += kWave) acc += col[k] * v[k];
-  acc = wave_sum_u(acc);
+  const double acc = dot.with(v);
   if (lane == 0) {
     if (xacc) xacc[r] += acc;
     else out[r] = acc;
@@ -1215,7 +1304,7 @@ sap_status run_lsqr(sap_ctx *ctx, const sap_problem *prob, const double *R, int6
     plan = plan_pass(ctx, refine ? 2 : mode, m, n, prob->lda, prob->A);
     plan_res = refine ? plan_pass(ctx, 3, m, n, prob->lda, prob->A) : plan;
   }
-  if (plan.grid > max_grid(ctx) || plan_res.grid > max_grid(ctx))
+  if (plan.grid > max_grid(ctx) || plan_res.grid > max_grid(ctx) || max_grid(ctx) > kMaxQSlices * kQSlice)
     return fail(ctx, SAP_EINVAL, "LSQR: internal grid larger than planned");
   LsqrBufs B = carve_lsqr(ctx, work, m, n);
   LsqrState *st = B.st;
@@ -1237,8 +1326,8 @@ sap_status run_lsqr(sap_ctx *ctx, const sap_problem *prob, const double *R, int6
   SAP_HIP_TRY(hipGetLastError());
 
   // One iteration = pass over A; q from the pass partials; v_hat = M^T q /
-  // beta - beta v; alpha, v, p = M v; rotation, x and w updates and the
-  // stopping test.
+  // beta - beta v; alpha, v, p = M v with the rotation, the x and w updates
+  // and the stopping test.
   auto iteration = [&](const PassPlan &pl, const void *pv, const void *uin, hipStream_t ls) {
     const int G = pl.grid;
     const int qsl = (G + kQSlice - 1) / kQSlice;
@@ -1248,10 +1337,10 @@ sap_status run_lsqr(sap_ctx *ctx, const sap_problem *prob, const double *R, int6
     else
       launch_pass(ctx, pl, prob->A, prob->lda, m, n, pv, uin, ubuf[ucur ^ 1], st, qpart, nrmpart, dyn, ls);
     ucur ^= 1;
-    q_slices_kernel<<<dim3((n + 63) / 64, qsl), 256, 0, ls>>>(qpart, G, n, qs);
+    q_slices_kernel<<<dim3((n + 63) / 64, qsl), 1024, 0, ls>>>(qpart, G, n, qs, st);
     lsqr_mtq_kernel<<<ngemv, 1024, 0, ls>>>(M, n, qs, qsl, nrmpart, G, v, vh, vpart, st);
-    lsqr_mv_kernel<<<ngemv, 1024, 0, ls>>>(Mt, n, vh, vpart, ngemv, nrmpart, G, v, p, refine ? p32 : nullptr, st);
-    lsqr_update_kernel<<<1, kTrsvThreads, 0, ls>>>(p, w, x, n, st);
+    lsqr_mv_kernel<<<ngemv, 1024, 0, ls>>>(Mt, n, vh, vpart, ngemv, nrmpart, G, v, p, refine ? p32 : nullptr, w, x,
+                                           ticket, st);
   };
 
   const int batch = 8;
@@ -1348,7 +1437,7 @@ sap_status run_hbm(sap_ctx *ctx, const sap_problem *prob, const double *R, int64
   if (n > kMaxN) return fail(ctx, SAP_EINVAL, "momentum: n > 8192 is not supported");
   if (mode != 0 && mode != 1) return fail(ctx, SAP_EINVAL, "momentum: mode must be FP64 or MIXED_FP32");
   const PassPlan plan = plan_pass(ctx, mode, m, n, prob->lda, prob->A);
-  if (plan.grid > max_grid(ctx)) return fail(ctx, SAP_EINVAL, "momentum: internal grid larger than planned");
+  if (plan.grid > max_grid(ctx) || max_grid(ctx) > kMaxQSlices * kQSlice) return fail(ctx, SAP_EINVAL, "momentum: internal grid larger than planned");
   LsqrBufs B = carve_lsqr(ctx, work, m, n);
   sap_status sst = setup_precond(ctx, R, ldr, nullptr, z, x, B, n, s);
   if (sst != SAP_OK) return sst;
@@ -1369,7 +1458,7 @@ sap_status run_hbm(sap_ctx *ctx, const sap_problem *prob, const double *R, int64
   auto launch_batch = [&](hipStream_t ls) {
     for (int k = 0; k < batch; ++k) {
       launch_pass(ctx, plan, prob->A, prob->lda, m, n, x, prob->b, B.ubuf[0], st, B.qpart, B.nrmpart, B.dyn, ls);
-      q_slices_kernel<<<dim3((n + 63) / 64, qsl), 256, 0, ls>>>(B.qpart, G, n, B.qs);
+      q_slices_kernel<<<dim3((n + 63) / 64, qsl), 1024, 0, ls>>>(B.qpart, G, n, B.qs, st);
       hbm_mtq_kernel<<<B.ngemv, 1024, 0, ls>>>(B.M, n, B.qs, qsl, sv, B.vpart, st);
       hbm_step_kernel<<<B.ngemv, 1024, 0, ls>>>(B.Mt, n, sv, B.vpart, B.ngemv, B.nrmpart, G, alpha, beta, delta, x,
                                                 st);
@@ -1427,7 +1516,7 @@ sap_status run_sstep(sap_ctx *ctx, const sap_problem *prob, const double *R, int
   if (mode != 0 && mode != 1) return fail(ctx, SAP_EINVAL, "s-step: mode must be FP64 or MIXED_FP32");
   if (S < 1 || S > kMaxSstep || !(hi > lo)) return fail(ctx, SAP_EINVAL, "s-step: bad block size or interval");
   const PassPlan plan = plan_pass(ctx, mode, m, n, prob->lda, prob->A);
-  if (plan.grid > max_grid(ctx)) return fail(ctx, SAP_EINVAL, "s-step: internal grid larger than planned");
+  if (plan.grid > max_grid(ctx) || max_grid(ctx) > kMaxQSlices * kQSlice) return fail(ctx, SAP_EINVAL, "s-step: internal grid larger than planned");
   LsqrBufs B = carve_lsqr(ctx, work, m, n);
   sap_status sst = setup_precond(ctx, R, ldr, nullptr, z, x, B, n, s);
   if (sst != SAP_OK) return sst;
@@ -1453,7 +1542,7 @@ sap_status run_sstep(sap_ctx *ctx, const sap_problem *prob, const double *R, int
   // r = b - A x, q = A^T r, out = M^T q (and its norm partials in B.vpart)
   auto product = [&](const double *pv, LsqrState *pst, double *out) {
     launch_pass(ctx, plan, prob->A, prob->lda, m, n, pv, prob->b, B.ubuf[0], pst, B.qpart, B.nrmpart, B.dyn, s);
-    q_slices_kernel<<<dim3((n + 63) / 64, qsl), 256, 0, s>>>(B.qpart, G, n, B.qs);
+    q_slices_kernel<<<dim3((n + 63) / 64, qsl), 1024, 0, s>>>(B.qpart, G, n, B.qs, pst);
     hbm_mtq_kernel<<<B.ngemv, 1024, 0, s>>>(B.M, n, B.qs, qsl, out, B.vpart, pst);
   };
   auto *hn = static_cast<double *>(ctx->pinned);  // rn, ||r0||, ||b||, error flag

@@ -126,37 +126,71 @@ __device__ __forceinline__ void chain_block(const double *__restrict__ M, int64_
   publish_flag(&flags[b], epoch);
 }
 
-// Inverse of diagonal block b of R (upper) and its transpose (for R^T);
-// 256 threads, column c of the inverse by back substitution of R_bb x = e_c.
+// Inverse of diagonal block b of R (upper) and its transpose (for R^T); 256
+// threads.  The block's four 16 x 16 diagonal blocks are inverted at once, one
+// a wave (a lane a column, back substitution in registers), then joined twice
+// by X12 = -X11 (R12 X22).  One thread a column over the whole block is a
+// chain of 2016 dependent LDS products (49 us; this form 17).
 struct TrsvPrepShared {
   double Rb[kTrsvB][kTrsvB + 1];
   double X[kTrsvB][kTrsvB + 1];  // X[row][col] = (R_bb^-1)(row, col)
+  double T[kTrsvB / 2][kTrsvB / 2 + 1];
 };
+
+// X12 = -X11 (R12 X22) for the blocks of H rows at o and o + H, by `threads`
+// threads (t of them), T: their H x H scratch.  Two barriers, taken by all.
+template <int H>
+__device__ __forceinline__ void trsv_join(TrsvPrepShared &sh, int o, int t, int threads, int trow) {
+  for (int e = t; e < H * H; e += threads) {
+    const int r = e / H, c = e % H;
+    double s = 0.0;
+#pragma unroll 8
+    for (int k = 0; k < H; ++k) s += sh.Rb[o + r][o + H + k] * sh.X[o + H + k][o + H + c];
+    sh.T[trow + r][c] = s;
+  }
+  __syncthreads();
+  for (int e = t; e < H * H; e += threads) {
+    const int r = e / H, c = e % H;
+    double s = 0.0;
+#pragma unroll 8
+    for (int k = 0; k < H; ++k) s += sh.X[o + r][o + k] * sh.T[trow + k][c];
+    sh.X[o + r][o + H + c] = -s;
+  }
+  __syncthreads();
+}
 
 __device__ __forceinline__ void trsv_invert_diag_block(const double *__restrict__ R, int64_t ldr, int n, int b,
                                                        double *__restrict__ Dup, double *__restrict__ Dlo,
                                                        TrsvPrepShared &sh) {
+  constexpr int Q = kTrsvB / 4;
+  const int t = threadIdx.x;
   const int k0 = b * kTrsvB;
   const int kn = min(kTrsvB, n - k0);
-  for (int e = threadIdx.x; e < kTrsvB * kTrsvB; e += blockDim.x) {
+  for (int e = t; e < kTrsvB * kTrsvB; e += blockDim.x) {
     const int rr = e % kTrsvB, cc = e / kTrsvB;
     sh.Rb[rr][cc] = (rr < kn && cc < kn && rr <= cc) ? R[(k0 + rr) + static_cast<int64_t>(k0 + cc) * ldr] : 0.0;
     sh.X[rr][cc] = 0.0;
   }
   __syncthreads();
-  const int c = threadIdx.x;
-  if (c < kn) {
-    sh.X[c][c] = 1.0 / sh.Rb[c][c];
-    for (int rr = c - 1; rr >= 0; --rr) {
-      double s = 0.0;
-      for (int k = rr + 1; k <= c; ++k) s += sh.Rb[rr][k] * sh.X[k][c];
-      sh.X[rr][c] = -s / sh.Rb[rr][rr];
+  const int o = Q * (t / kWave), c = t % kWave;
+  if (c < Q) {
+    double x[Q];
+#pragma unroll
+    for (int rr = Q - 1; rr >= 0; --rr) {
+      double s = rr == c ? 1.0 : 0.0;
+#pragma unroll
+      for (int k = rr + 1; k < Q; ++k) s -= sh.Rb[o + rr][o + k] * x[k];
+      // rows past the matrix's end stay zero, as do rows below the diagonal
+      x[rr] = (rr <= c && o + c < kn) ? s / sh.Rb[o + rr][o + rr] : 0.0;
+      sh.X[o + rr][o + c] = x[rr];
     }
   }
   __syncthreads();
+  trsv_join<Q>(sh, 2 * Q * (t / (2 * kWave)), t % (2 * kWave), 2 * kWave, Q * (t / (2 * kWave)));
+  trsv_join<2 * Q>(sh, 0, t, 4 * kWave, 0);
   double *du = Dup + static_cast<int64_t>(b) * kTrsvB * kTrsvB;
   double *dl = Dlo + static_cast<int64_t>(b) * kTrsvB * kTrsvB;
-  for (int e = threadIdx.x; e < kTrsvB * kTrsvB; e += blockDim.x) {
+  for (int e = t; e < kTrsvB * kTrsvB; e += blockDim.x) {
     const int rr = e % kTrsvB, cc = e / kTrsvB;
     du[rr + cc * kTrsvB] = sh.X[rr][cc];  // col-major
     dl[rr + cc * kTrsvB] = sh.X[cc][rr];  // (R_bb^T)^-1 = (R_bb^-1)^T
