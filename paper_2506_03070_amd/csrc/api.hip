@@ -52,6 +52,13 @@ sap_status ensure_workspace(sap_ctx *ctx, size_t bytes, hipStream_t stream) {
   return SAP_OK;
 }
 
+sap_status ensure_workspace_upto(sap_ctx *ctx, size_t needed, size_t wanted, size_t *got, hipStream_t stream) {
+  *got = wanted;
+  if (wanted > needed && ensure_workspace(ctx, wanted, stream) == SAP_OK) return SAP_OK;
+  *got = needed;
+  return ensure_workspace(ctx, needed, stream);
+}
+
 static hipEvent_t take_event(sap_ctx *ctx) {
   if (!ctx->free_events.empty()) {
     hipEvent_t e = ctx->free_events.back();
@@ -269,10 +276,13 @@ sap_status sps_apply(sap_ctx *ctx, const sps_sketch *S, const void *A, int64_t l
   hipStream_t st = static_cast<hipStream_t>(stream);
   SAP_HIP_TRY(hipSetDevice(ctx->device));
   const int ncols = n + (b ? 1 : 0);
-  s = ensure_workspace(ctx, apply_workspace_bytes(ctx, S->m, S->zeta, S->d, ncols, y_type) + 256, st);
+  size_t got = 0;
+  s = ensure_workspace_upto(ctx, apply_workspace_bytes(ctx, S->m, S->zeta, S->d, ncols, y_type) + 256,
+                            apply_workspace_wanted(ctx, S->m, S->zeta, S->d, n, lda, b != nullptr, a_type, y_type) + 256,
+                            &got, st);
   if (s != SAP_OK) return s;
   hipEvent_t pb = prof_begin(ctx, st);
-  s = launch_apply(ctx, S, A, lda, a_type, b, n, Y, ldy, y_type, ctx->ws, st);
+  s = launch_apply(ctx, S, A, lda, a_type, b, n, Y, ldy, y_type, ctx->ws, got, st);
   prof_end(ctx, kProfApply, pb, st);
   return s;
 }
@@ -297,7 +307,7 @@ sap_status sps_apply_noalloc(sap_ctx *ctx, const sps_sketch *S, const void *A, i
                                      " bytes of scratch, more than the static buffer's " +
                                      std::to_string(ctx->apply_scratch_bytes));
   SAP_HIP_TRY(hipSetDevice(ctx->device));
-  return launch_apply(ctx, S, A, lda, a_type, b, n, Y, ldy, y_type, ctx->apply_scratch,
+  return launch_apply(ctx, S, A, lda, a_type, b, n, Y, ldy, y_type, ctx->apply_scratch, ctx->apply_scratch_bytes,
                       static_cast<hipStream_t>(stream));
 }
 
@@ -478,14 +488,20 @@ static sap_status solve_dense(sap_ctx *ctx, const sap_problem *prob, const sap_p
   const size_t bytes_lsqr = lsqr_workspace_bytes(ctx, m, n);
   size_t scratch = bytes_apply > bytes_qr ? bytes_apply : bytes_qr;
   scratch = scratch > bytes_lsqr ? scratch : bytes_lsqr;
+  const size_t scratch_fast =
+      std::max(scratch, apply_workspace_wanted(ctx, m, par->zeta, d, n,
+                                               mode == SAP_MODE_MIXED_BF16SA ? (n + 7) / 8 * 8 : prob->lda, true,
+                                               mode == SAP_MODE_MIXED_BF16SA ? SAP_BF16 : prob->a_type, y_type));
   const bool bf16sa = mode == SAP_MODE_MIXED_BF16SA;
   const int64_t ld_bf = (static_cast<int64_t>(n) + 7) / 8 * 8;
   const size_t bytes_bf = bf16sa ? static_cast<size_t>(m) * ld_bf * sizeof(__hip_bfloat16) : 0;
   const size_t bytes_ss = ss ? sstep_workspace_bytes(n, ss->s) : 0;
-  const size_t total =
-      10 * 256 + bytes_flags + bytes_idx + bytes_sign + bytes_Y + bytes_tau + bytes_bf + bytes_ss + scratch;
-  s = ensure_workspace(ctx, total, st);
+  const size_t fixed_bytes =
+      10 * 256 + bytes_flags + bytes_idx + bytes_sign + bytes_Y + bytes_tau + bytes_bf + bytes_ss;
+  size_t got = 0;
+  s = ensure_workspace_upto(ctx, fixed_bytes + scratch, fixed_bytes + scratch_fast, &got, st);
   if (s != SAP_OK) return s;
+  scratch = got - fixed_bytes;
   Carve cv(ctx->ws);
   SolveFlags *flags = cv.take<SolveFlags>(1);
   int32_t *idx = cv.take<int32_t>(static_cast<size_t>(m) * par->zeta);
@@ -521,8 +537,8 @@ static sap_status solve_dense(sap_ctx *ctx, const sap_problem *prob, const sap_p
     SAP_HIP_TRY(hipGetLastError());
   }
   hipEvent_t pb_apply = prof_begin(ctx, st);
-  s = bf16sa ? launch_apply(ctx, &S, Abf, ld_bf, SAP_BF16, prob->b, n, Y, d, y_type, work, st)
-             : launch_apply(ctx, &S, prob->A, prob->lda, prob->a_type, prob->b, n, Y, d, y_type, work, st);
+  s = bf16sa ? launch_apply(ctx, &S, Abf, ld_bf, SAP_BF16, prob->b, n, Y, d, y_type, work, scratch, st)
+             : launch_apply(ctx, &S, prob->A, prob->lda, prob->a_type, prob->b, n, Y, d, y_type, work, scratch, st);
   if (s != SAP_OK) return s;
   prof_end(ctx, kProfApply, pb_apply, st);
   SAP_HIP_TRY(hipEventRecord(ev[2], st));

@@ -231,6 +231,9 @@ sap_status hip_fail(sap_ctx *ctx, hipError_t e, const char *what);
 // Grow the context workspace to at least `bytes` (synchronises `stream` when
 // it has to reallocate).  Returns SAP_ENOMEM beyond the budget.
 sap_status ensure_workspace(sap_ctx *ctx, size_t bytes, hipStream_t stream);
+// The same for `wanted` bytes where the budget and the device's memory allow
+// it, else for `needed`; *got receives which of the two.
+sap_status ensure_workspace_upto(sap_ctx *ctx, size_t needed, size_t wanted, size_t *got, hipStream_t stream);
 
 // Bump allocator over a workspace region (256-byte aligned pieces).
 struct Carve {
@@ -258,11 +261,14 @@ void prof_resolve(sap_ctx *ctx);
 // Sketch generation (sketch.hip).
 sap_status launch_generate(sap_ctx *ctx, const sps_sketch *S, int *err_word, hipStream_t st);
 
-// Sketch apply (apply.hip).  Workspace bytes for partial sums first.
+// Sketch apply (apply.hip): the workspace it needs, and what it can use to run
+// faster; launch_apply takes whatever it is given from the first on.
 size_t apply_workspace_bytes(sap_ctx *ctx, int64_t m, int zeta, int d, int ncols, sap_dtype y_type);
+size_t apply_workspace_wanted(sap_ctx *ctx, int64_t m, int zeta, int d, int n, int64_t lda, bool with_b,
+                              sap_dtype a_type, sap_dtype y_type);
 sap_status launch_apply(sap_ctx *ctx, const sps_sketch *S, const void *A, int64_t lda,
                         sap_dtype a_type, const double *b, int n, void *Y, int64_t ldy,
-                        sap_dtype y_type, void *work, hipStream_t st);
+                        sap_dtype y_type, void *work, size_t work_bytes, hipStream_t st);
 
 // Static scratch of the allocation-free apply (apply.hip): its size, and the
 // lookup of this device's copy (once per context, with the device current).
