@@ -20,6 +20,19 @@ struct Block4 {
   uint64_t w[4];
 };
 
+// 128-bit product from four 32 x 32 + 64 multiply-adds (v_mad_u64_u32).  The
+// generator is bound by these quarter-rate multiplies (60 products a column at
+// zeta = 8); low and high half asked for separately take seven.
+__device__ __forceinline__ void mul_wide(uint64_t a, uint64_t b, uint64_t &lo, uint64_t &hi) {
+  const uint32_t a0 = static_cast<uint32_t>(a), a1 = static_cast<uint32_t>(a >> 32);
+  const uint32_t b0 = static_cast<uint32_t>(b), b1 = static_cast<uint32_t>(b >> 32);
+  const uint64_t p00 = static_cast<uint64_t>(a0) * b0;
+  const uint64_t p01 = static_cast<uint64_t>(a0) * b1 + (p00 >> 32);
+  const uint64_t p10 = static_cast<uint64_t>(a1) * b0 + static_cast<uint32_t>(p01);
+  hi = static_cast<uint64_t>(a1) * b1 + (p01 >> 32) + (p10 >> 32);
+  lo = (p10 << 32) | static_cast<uint32_t>(p00);
+}
+
 __device__ __forceinline__ Block4 philox(uint64_t c0, uint64_t c1, uint64_t c2, uint64_t c3,
                                          uint64_t k0, uint64_t k1) {
 #pragma unroll
@@ -28,8 +41,9 @@ __device__ __forceinline__ Block4 philox(uint64_t c0, uint64_t c1, uint64_t c2, 
       k0 += kPhiloxW0;
       k1 += kPhiloxW1;
     }
-    const uint64_t lo0 = kPhiloxM0 * c0, hi0 = __umul64hi(kPhiloxM0, c0);
-    const uint64_t lo1 = kPhiloxM1 * c2, hi1 = __umul64hi(kPhiloxM1, c2);
+    uint64_t lo0, hi0, lo1, hi1;
+    mul_wide(kPhiloxM0, c0, lo0, hi0);
+    mul_wide(kPhiloxM1, c2, lo1, hi1);
     const uint64_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
     c0 = n0;
     c1 = lo1;
@@ -151,9 +165,20 @@ __device__ __forceinline__ void generate_column(int64_t i, int d, int zeta, uint
   }
 
   int32_t *out = idx + i * zeta;
+  bool stored = false;
+  if constexpr (ZMAX == 8) {  // a lane's 32 bytes in two stores instead of eight
+    if (zeta == 8 && (reinterpret_cast<uintptr_t>(idx) & 15) == 0) {
+      int4 *o4 = reinterpret_cast<int4 *>(out);
+      o4[0] = make_int4(c[0], c[1], c[2], c[3]);
+      o4[1] = make_int4(c[4], c[5], c[6], c[7]);
+      stored = true;
+    }
+  }
+  if (!stored) {
 #pragma unroll
-  for (int j = 0; j < ZMAX; ++j)
-    if (j < zeta) out[j] = static_cast<int32_t>(c[j]);
+    for (int j = 0; j < ZMAX; ++j)
+      if (j < zeta) out[j] = static_cast<int32_t>(c[j]);
+  }
   const Block4 s = philox(col, ~0ull, 0, 0, seed, stream);
   const uint64_t mask = (zeta >= 64) ? ~0ull : ((1ull << zeta) - 1ull);
   sign[i] = s.w[0] & mask;
