@@ -36,10 +36,13 @@
 #include <cmath>
 #include <type_traits>
 
+#include "apply_dev.h"
 #include "common.h"
 
 namespace sap {
 namespace {
+
+using namespace apply_dev;
 
 constexpr int kApplyThreads = 1024;
 constexpr int kApplyWaves = kApplyThreads / kWave;
@@ -59,14 +62,14 @@ __device__ __forceinline__ T load_as(const TA *p) {
 }
 
 // One work item = (strip, range, slice).
-// FAST (one range, zeta = 8, idx 16-byte aligned): per row two 16-byte index
-// loads, every load of a batch of rows issued before any add, and no
-// branches: a row past the slice end adds zeros, and an index outside [0, d)
-// adds into a spare LDS row that is never written out.  Otherwise the
-// general path loads the indices four at a time and skips indices outside
-// the range.
-// C16 (with FAST): row indices and signs come from a 16-bit copy (idx16, 8 per
-// row, one 16-byte load), for sketches that many strips re-read.
+// FORM 2 (one range, zeta = 8, a packed copy of the sketch): add_rows_packed,
+// but for the strip that holds b's column beside A's.
+// FORM 1 (one range, zeta = 8, idx 16-byte aligned; where the copy does not pay
+// or has no room in the workspace): per row two 16-byte index loads, every load of a batch
+// of rows issued before any add, and no branches: a row past the slice end
+// adds zeros, and an index outside [0, d) adds into a spare LDS row that is
+// never written out.
+// FORM 0: indices four at a time, those outside the range skipped.
 // The strip fills the LDS, so a CU holds one workgroup (4 waves a SIMD);
 // telling the compiler so lets it keep every load of a batch in flight
 // instead of trading registers for an occupancy it never gets.
@@ -74,9 +77,9 @@ __device__ __forceinline__ T load_as(const TA *p) {
 // instruction on gfx950 in every access pattern, ds_add_f64 9.5 to 26
 // (300007 x 513 FP32, d = 2052, FP32 Y: 12.1 ms with FP32 sums).
 // run_if (nullable): the launch does nothing unless *run_if is set.
-template <typename TA, typename TO, int W, bool FAST, bool C16>
+template <typename TA, typename TO, int W, int FORM>
 __global__ __launch_bounds__(kApplyThreads) __attribute__((amdgpu_waves_per_eu(1, 4))) void apply_strip_kernel(
-    const int32_t *__restrict__ idx, const uint16_t *__restrict__ idx16, const uint64_t *__restrict__ sign,
+    const int32_t *__restrict__ idx, const uint4 *__restrict__ packed, const uint64_t *__restrict__ sign,
     int zeta, const TA *__restrict__ A,
     int64_t lda, const double *__restrict__ b, int64_t m, int n, int ncols, int d, int dr, int nstrips,
     int nranges, int nslices, int64_t rows_per_slice, TO *__restrict__ out, int64_t ldo, int64_t slice_stride,
@@ -99,7 +102,7 @@ __global__ __launch_bounds__(kApplyThreads) __attribute__((amdgpu_waves_per_eu(1
   const int r_lo = range * dr;
   const int rows_here = min(dr, d - r_lo);
 
-  for (int e = threadIdx.x; e < (rows_here + (FAST ? 1 : 0)) * W; e += kApplyThreads) acc[e] = 0.0;
+  for (int e = threadIdx.x; e < (rows_here + (FORM != 0 ? 1 : 0)) * W; e += kApplyThreads) acc[e] = 0.0;
   __syncthreads();
 
   const int64_t i_begin = static_cast<int64_t>(slice) * rows_per_slice;
@@ -110,12 +113,14 @@ __global__ __launch_bounds__(kApplyThreads) __attribute__((amdgpu_waves_per_eu(1
   const bool col_a = col < n;
   const bool col_b = (col == n) && (col < ncols);
   constexpr int64_t kStride = static_cast<int64_t>(kApplyWaves) * RPW * kUnroll;
-  for (int64_t base = i_begin + wave * (RPW * kUnroll) + g; base < i_end; base += kStride) {
-    if constexpr (FAST) {
+  const bool packed_strip = FORM == 2 && (c0 + W <= n || ncols == n);  // uniform: no lane takes b
+  if constexpr (FORM == 2) {
+    if (packed_strip) add_rows_packed<TA, W>(acc, A, lda, n, c0, packed, i_begin, i_end, kApplyWaves);
+  }
+  for (int64_t base = i_begin + wave * (RPW * kUnroll) + g; base < i_end && !packed_strip; base += kStride) {
+    if constexpr (FORM == 2) {
       double val[kUnroll];
-      uint32_t sg[kUnroll];
-      int4 ix[kUnroll][2];
-      uint4 raw[kUnroll];  // 16-bit copy: decoded after every load of the batch is issued
+      uint4 raw[kUnroll];
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
         const int64_t i0 = base + u * RPW;
@@ -125,37 +130,36 @@ __global__ __launch_bounds__(kApplyThreads) __attribute__((amdgpu_waves_per_eu(1
         if (col_a) a = load_as<TA, double>(A + i * lda + col);
         else if (col_b) a = b[i];
         val[u] = ok ? a : 0.0;
-        if constexpr (C16) {
-          raw[u] = *reinterpret_cast<const uint4 *>(idx16 + i * 8);
-        } else {
-          sg[u] = static_cast<uint32_t>(sign[i]);
-          const int4 *ip = reinterpret_cast<const int4 *>(idx + i * 8);
-          ix[u][0] = ip[0];
-          ix[u][1] = ip[1];
-        }
+        raw[u] = packed[i];
+      }
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) add_packed<W>(acc, c, raw[u], val[u]);
+    } else if constexpr (FORM == 1) {
+      double val[kUnroll];
+      uint32_t sg[kUnroll];
+      int4 ix[kUnroll][2];
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u) {
+        const int64_t i0 = base + u * RPW;
+        const bool ok = i0 < i_end;
+        const int64_t i = ok ? i0 : i_end - 1;
+        double a = 0.0;
+        if (col_a) a = load_as<TA, double>(A + i * lda + col);
+        else if (col_b) a = b[i];
+        val[u] = ok ? a : 0.0;
+        sg[u] = static_cast<uint32_t>(sign[i]);
+        const int4 *ip = reinterpret_cast<const int4 *>(idx + i * 8);
+        ix[u][0] = ip[0];
+        ix[u][1] = ip[1];
       }
 #pragma unroll
       for (int u = 0; u < kUnroll; ++u) {
-        int rr[8];
-        bool pos[8];
-        if constexpr (C16) {
-          const uint32_t wd[4] = {raw[u].x, raw[u].y, raw[u].z, raw[u].w};
-#pragma unroll
-          for (int k = 0; k < 8; ++k) {
-            const uint32_t half = (k & 1) ? (wd[k >> 1] >> 16) : (wd[k >> 1] & 0xFFFFu);
-            rr[k] = static_cast<int>(half & 0x7FFFu);
-            pos[k] = (half & 0x8000u) != 0;
-          }
-        } else {
-          rr[0] = ix[u][0].x; rr[1] = ix[u][0].y; rr[2] = ix[u][0].z; rr[3] = ix[u][0].w;
-          rr[4] = ix[u][1].x; rr[5] = ix[u][1].y; rr[6] = ix[u][1].z; rr[7] = ix[u][1].w;
-#pragma unroll
-          for (int k = 0; k < 8; ++k) pos[k] = ((sg[u] >> k) & 1u) != 0;
-        }
+        const int rr[8] = {ix[u][0].x, ix[u][0].y, ix[u][0].z, ix[u][0].w,
+                           ix[u][1].x, ix[u][1].y, ix[u][1].z, ix[u][1].w};
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
           const int r = static_cast<unsigned>(rr[k]) < static_cast<unsigned>(d) ? rr[k] : d;
-          atomicAdd(acc + r * W + c, pos[k] ? val[u] : -val[u]);
+          atomicAdd(acc + r * W + c, ((sg[u] >> k) & 1u) ? val[u] : -val[u]);
         }
       }
     } else {
@@ -218,23 +222,22 @@ __global__ __launch_bounds__(256) void apply_reduce_kernel(const TO *__restrict_
   Y[r + static_cast<int64_t>(c) * ldy] = static_cast<TO>(s) * static_cast<TO>(h);
 }
 
-// 16-bit copy of the row indices and signs (zeta = 8, d <= 32767): the index in
-// bits 0-14 (one outside [0, d) becomes 0x7FFF >= d, which the apply adds into
-// its spare row), the sign (bit k of the row's sign word) in bit 15.
-__global__ __launch_bounds__(256) void idx16_kernel(const int32_t *__restrict__ idx,
-                                                    const uint64_t *__restrict__ sign, int64_t count, int d,
-                                                    uint16_t *__restrict__ out, const int *__restrict__ run_if) {
+// The packed copy (zeta = 8, d <= kPackMaxD), one row a thread.
+__global__ __launch_bounds__(256) void pack_rows_kernel(const int32_t *__restrict__ idx,
+                                                        const uint64_t *__restrict__ sign, int64_t m, int d,
+                                                        uint4 *__restrict__ out, const int *__restrict__ run_if) {
   if (run_if && *run_if == 0) return;
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * 256;
-  for (int64_t e = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; e < count; e += stride) {
-    const int32_t v = idx[e];
-    const uint32_t s = static_cast<uint32_t>(sign[e >> 3] >> (e & 7)) & 1u;
-    out[e] = static_cast<uint16_t>((v >= 0 && v < d ? v : 0x7FFF) | (s << 15));
-  }
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (i >= m) return;
+  const uint32_t s = static_cast<uint32_t>(sign[i]);
+  uint32_t e[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) e[k] = pack_entry(idx[i * 8 + k], d, (s >> k) & 1u);
+  out[i] = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
 }
 
-// The strips re-read every row's indices and sign word (40 bytes); past this
-// many bytes of such re-reads the 16-bit copy (16 bytes a row) pays for itself.
+// What apply_workspace_bytes counts a packed copy for (a size that callers'
+// limits are held against): this many bytes of strips re-reading 40 bytes a row.
 constexpr double kCompactMinRereadBytes = 16e9;
 
 // ---- gather form -------------------------------------------------------------
@@ -536,15 +539,21 @@ ApplyPlan make_plan(int num_cus, int64_t m, int d, int ncols, size_t esize) {
 }
 
 // Time estimates (us) that the choices below compare; measured on one MI355X.
-// Clocks per wave instruction of 64 adds in the scatter form, index loads and
-// bank conflicts included: 10 for W = 32, 12, 14, 20 (d = 4000), 31 (8000), 49
-// (12000) for W = 1; half as much again on the general path (zeta != 8).
-double scatter_us(int num_cus, int64_t m, int zeta, int ncols, const ApplyPlan &p) {
-  const double clk = (p.w >= 32 ? 10 : p.w == 16 ? 12 : p.w == 8 ? 14 : p.w == 4 ? 20 : p.w == 2 ? 31 : 49) *
-                     (zeta == 8 && p.nranges == 1 ? 1.0 : 1.5) * p.nranges;
+// Cycles of a CU for 64 adds in the scatter form, loads and bank conflicts
+// included, with packed rows: 10.5 for W = 32 and 16, 13.5, 18.5 (d = 4000), 25
+// (8000), 33 (12000) for W = 1; 3 more from the 32-bit indices, half as much
+// again on the general path (zeta != 8).
+double scatter_us(int num_cus, int zeta, const ApplyPlan &p, bool pack) {
+  const double clk = ((p.w >= 16 ? 10.5 : p.w == 8 ? 13.5 : p.w == 4 ? 18.5 : p.w == 2 ? 25 : 33) *
+                          (zeta == 8 && p.nranges == 1 ? 1.0 : 1.5) +
+                      (pack ? 0 : 3)) *
+                     p.nranges;
   const double items = static_cast<double>(p.nstrips) * p.nranges * p.nslices;
   const double rounds = std::ceil(items / num_cus);
-  const double strip = (static_cast<double>(p.rows_per_slice) * zeta * p.w / 64.0) * clk / 2400.0 / p.nranges;
+  // whole batches of rows of the 16 waves, a short last one as long as the others
+  const int64_t step = static_cast<int64_t>(kApplyWaves) * (kWave / p.w) * kUnroll;
+  const double rows = static_cast<double>((p.rows_per_slice + step - 1) / step * step);
+  const double strip = (rows * zeta * p.w / 64.0) * clk / 2400.0 / p.nranges;
   return rounds * (strip + 5.0);  // 5: the strip cleared and written out
 }
 // Partial strips written and read back at about 4 TB/s.
@@ -556,15 +565,15 @@ double parts_us(int nslices, int d, int ncols, size_t es) {
 // items on 256 CUs take as long as 512 (300007 x 513, d = 2052), and 4 strips of
 // 20000 rows in slices of 4096 keep 16 CUs busy (20000 x 100, d = 400: 114 us,
 // 33 in slices of 512).
-ApplyPlan fine_plan(int num_cus, int64_t m, int zeta, int d, int ncols, size_t es, const ApplyPlan &p) {
+ApplyPlan fine_plan(int num_cus, int64_t m, int zeta, int d, int ncols, size_t es, const ApplyPlan &p, bool pack) {
   ApplyPlan best = p;
-  double best_us = scatter_us(num_cus, m, zeta, ncols, p) + parts_us(p.nslices, d, ncols, es);
-  const int most = static_cast<int>(std::min<int64_t>(64, std::max<int64_t>(1, m / kFineSliceRows)));
+  double best_us = scatter_us(num_cus, zeta, p, pack) + parts_us(p.nslices, d, ncols, es);
+  const int most = static_cast<int>(std::min<int64_t>(64, (m + kFineSliceRows - 1) / kFineSliceRows));
   for (int ns = 1; ns <= most; ++ns) {
     ApplyPlan q = p;
     q.rows_per_slice = (m + ns - 1) / ns;
     q.nslices = static_cast<int>((m + q.rows_per_slice - 1) / q.rows_per_slice);
-    const double us = scatter_us(num_cus, m, zeta, ncols, q) + parts_us(q.nslices, d, ncols, es);
+    const double us = scatter_us(num_cus, zeta, q, pack) + parts_us(q.nslices, d, ncols, es);
     if (us < 0.98 * best_us) {
       best_us = us;
       best = q;
@@ -573,9 +582,13 @@ ApplyPlan fine_plan(int num_cus, int64_t m, int zeta, int d, int ncols, size_t e
   return best;
 }
 
-bool wants_compact(const ApplyPlan &p, int64_t m, int zeta, int d_max, int d) {
-  return zeta == 8 && p.nranges == 1 && d <= d_max &&
-         static_cast<double>(p.nstrips) * static_cast<double>(m) * 40.0 >= kCompactMinRereadBytes;
+// Whether the strips read a packed copy: it saves about 3 cycles of a CU for 64
+// adds (200000 x 257, d = 1024: 191 -> 141 us; 65536 x 501, d = 2600: 165 -> 142)
+// and costs a launch and 56 bytes a row (20000 x 101, d = 400: 31 -> 33 us).
+bool wants_pack(int num_cus, int64_t m, int zeta, int d, int64_t lda, const ApplyPlan &p) {
+  if (zeta != 8 || p.nranges != 1 || d > kPackMaxD || lda >= (int64_t(1) << 31) / (8 * kWave * kPackRows)) return false;
+  const double adds = static_cast<double>(m) * zeta * p.nstrips * p.w / 64.0;
+  return adds / num_cus * 3.0 / 2400.0 > 4.0 + static_cast<double>(m) * 56.0 / 4e6;
 }
 
 size_t part_bytes(int nslices, int d, int ncols, size_t es) {
@@ -630,7 +643,7 @@ GatherPlan make_gather(int num_cus, int64_t m, int zeta, int d, int n, int64_t l
     }
   }
   const double lists = 50.0 + std::ceil(static_cast<double>(g.ntiles) / num_cus) * g.rows * zeta * 1e-3;
-  if (best + lists > 0.95 * scatter) return g;
+  if (best + lists > 0.97 * scatter) return g;
   const double cap = static_cast<double>(g.ntiles) * groups * ((longest + 3.0) / 4.0) + 1024.0;
   if (cap > 2.0e9) return g;
   g.cap = static_cast<unsigned>(cap);
@@ -645,7 +658,7 @@ GatherPlan make_gather(int num_cus, int64_t m, int zeta, int d, int n, int64_t l
 struct FullPlan {
   ApplyPlan all, a, b;
   GatherPlan g;
-  bool compact;
+  bool pack;
   size_t scatter_bytes, gather_bytes;
 };
 FullPlan full_plan(int num_cus, int64_t m, int zeta, int d, int n, int64_t lda, bool with_b, sap_dtype a_type,
@@ -653,14 +666,14 @@ FullPlan full_plan(int num_cus, int64_t m, int zeta, int d, int n, int64_t lda, 
   FullPlan f;
   const int ncols = n + (with_b ? 1 : 0);
   const ApplyPlan p = make_plan(num_cus, m, d, ncols, sizeof(double));
-  f.all = fine_plan(num_cus, m, zeta, d, ncols, es, p);
-  f.compact = wants_compact(p, m, zeta, 32767, d);
-  const size_t copy = f.compact ? static_cast<size_t>(m) * 16 + 256 : 0;
+  f.pack = wants_pack(num_cus, m, zeta, d, lda, p);
+  f.all = fine_plan(num_cus, m, zeta, d, ncols, es, p, f.pack);
+  const size_t copy = f.pack ? static_cast<size_t>(m) * 16 + 256 : 0;
   f.scatter_bytes = part_bytes(f.all.nslices, d, ncols, es) + copy + 1024;
   f.a = make_plan(num_cus, m, d, n, sizeof(double));
-  f.b = fine_plan(num_cus, m, zeta, d, 1, es, make_plan(num_cus, m, d, 1, sizeof(double)));
+  f.b = fine_plan(num_cus, m, zeta, d, 1, es, make_plan(num_cus, m, d, 1, sizeof(double)), false);
   f.g = make_gather(num_cus, m, zeta, d, n, lda, a_type, es,
-                    scatter_us(num_cus, m, zeta, ncols, f.all) + parts_us(f.all.nslices, d, ncols, es));
+                    scatter_us(num_cus, zeta, f.all, f.pack) + parts_us(f.all.nslices, d, ncols, es));
   f.gather_bytes = f.g.use ? f.g.bytes + part_bytes(f.a.nslices, d, n, es) + copy +
                                  (with_b ? part_bytes(f.b.nslices, d, 1, es) : 0) + 2048
                            : 0;
@@ -670,24 +683,22 @@ FullPlan full_plan(int num_cus, int64_t m, int zeta, int d, int n, int64_t lda, 
 template <typename TA, typename TO, int W>
 void launch_strip(const ApplyPlan &p, dim3 grid, size_t lds, hipStream_t st, const sps_sketch *S, const TA *A,
                   int64_t lda, const double *b, int n, int ncols, TO *out, int64_t ldo, int64_t slice_stride,
-                  double h, int scale_now, const uint16_t *idx16, const int *run_if) {
-  // The 16-bit copy is read with 16-byte loads whatever S->idx's alignment
-  // (the copy is 256-byte aligned); the 32-bit indices only when S->idx is.
+                  double h, int scale_now, const uint4 *packed, const int *run_if) {
   const bool fast = S->zeta == 8 && p.nranges == 1 && (reinterpret_cast<uintptr_t>(S->idx) % 16 == 0);
-#define SAP_STRIP(FAST, C16, I16)                                                                                  \
-  apply_strip_kernel<TA, TO, W, FAST, C16><<<grid, kApplyThreads, lds, st>>>(                                     \
-      S->idx, I16, S->sign, S->zeta, A, lda, b, S->m, n, ncols, S->d, p.dr, p.nstrips, p.nranges, p.nslices,      \
+#define SAP_STRIP(FORM)                                                                                           \
+  apply_strip_kernel<TA, TO, W, FORM><<<grid, kApplyThreads, lds, st>>>(                                          \
+      S->idx, packed, S->sign, S->zeta, A, lda, b, S->m, n, ncols, S->d, p.dr, p.nstrips, p.nranges, p.nslices,   \
       p.rows_per_slice, out, ldo, slice_stride, h, scale_now, run_if)
-  if (idx16 != nullptr) SAP_STRIP(true, true, idx16);
-  else if (fast) SAP_STRIP(true, false, nullptr);
-  else SAP_STRIP(false, false, nullptr);
+  if (packed != nullptr) SAP_STRIP(2);
+  else if (fast) SAP_STRIP(1);
+  else SAP_STRIP(0);
 #undef SAP_STRIP
 }
 
 // The scatter form for columns 0 .. ncols-1 of [A b] into Y.
 template <typename TA, typename TO>
 sap_status scatter(sap_ctx *ctx, const sps_sketch *S, const TA *A, int64_t lda, const double *b, int n, int ncols,
-                   const ApplyPlan &p, bool compact, TO *Y, int64_t ldy, Carve &cv, const int *run_if,
+                   const ApplyPlan &p, bool pack, TO *Y, int64_t ldy, Carve &cv, const int *run_if,
                    hipStream_t st) {
   const double h = 1.0 / std::sqrt(static_cast<double>(S->zeta));
   TO *out = Y;
@@ -699,21 +710,19 @@ sap_status scatter(sap_ctx *ctx, const sps_sketch *S, const TA *A, int64_t lda, 
     slice_stride = static_cast<int64_t>(S->d) * ncols;
     scale_now = 0;
   }
-  const uint16_t *idx16 = nullptr;
-  if (compact) {
-    uint16_t *c = cv.take<uint16_t>(static_cast<size_t>(S->m) * 8);
-    const int64_t count = S->m * 8;
-    const unsigned g = static_cast<unsigned>(std::min<int64_t>((count + 255) / 256, int64_t(ctx->num_cus) * 16));
-    idx16_kernel<<<g, 256, 0, st>>>(S->idx, S->sign, count, S->d, c, run_if);
+  const uint4 *packed = nullptr;
+  if (pack) {
+    uint4 *c = cv.take<uint4>(static_cast<size_t>(S->m));
+    pack_rows_kernel<<<static_cast<unsigned>((S->m + 255) / 256), 256, 0, st>>>(S->idx, S->sign, S->m, S->d, c, run_if);
     SAP_HIP_TRY(hipGetLastError());
-    idx16 = c;
+    packed = c;
   }
   const int total = p.nstrips * p.nranges * p.nslices;
   const int per_xcd = (total + kXcds - 1) / kXcds;
   const dim3 grid(static_cast<unsigned>(per_xcd * kXcds));
   const size_t lds = (static_cast<size_t>(p.dr) + 1) * p.w * sizeof(double);
 #define SAP_STRIP_W(W) \
-  launch_strip<TA, TO, W>(p, grid, lds, st, S, A, lda, b, n, ncols, out, ldo, slice_stride, h, scale_now, idx16, run_if)
+  launch_strip<TA, TO, W>(p, grid, lds, st, S, A, lda, b, n, ncols, out, ldo, slice_stride, h, scale_now, packed, run_if)
   switch (p.w) {
     case 1: SAP_STRIP_W(1); break;
     case 2: SAP_STRIP_W(2); break;
@@ -792,17 +801,17 @@ sap_status apply_typed(sap_ctx *ctx, const sps_sketch *S, const TA *A, int64_t l
     int *flag = nullptr;
     sap_status s = gather<TA, TO>(ctx, S, A, lda, n, f.g, Y, ldy, cv, &flag, st);
     if (s != SAP_OK) return s;
-    s = scatter<TA, TO>(ctx, S, A, lda, nullptr, n, n, f.a, f.compact, Y, ldy, cv, flag, st);
+    s = scatter<TA, TO>(ctx, S, A, lda, nullptr, n, n, f.a, f.pack, Y, ldy, cv, flag, st);
     if (s != SAP_OK || b == nullptr) return s;
     return scatter<TA, TO>(ctx, S, nullptr, 1, b, 0, 1, f.b, false, Y + static_cast<int64_t>(n) * ldy, ldy, cv,
                            nullptr, st);
   }
   if (f.scatter_bytes > work_bytes) {  // what apply_workspace_bytes counts
     f.all = make_plan(ctx->num_cus, S->m, S->d, ncols, sizeof(double));
-    f.compact = f.compact && part_bytes(f.all.nslices, S->d, ncols, sizeof(TO)) +
-                                     static_cast<size_t>(S->m) * 16 + 1280 <= work_bytes;
+    f.pack = f.pack && part_bytes(f.all.nslices, S->d, ncols, sizeof(TO)) + static_cast<size_t>(S->m) * 16 + 1280 <=
+                           work_bytes;
   }
-  return scatter<TA, TO>(ctx, S, A, lda, b, n, ncols, f.all, f.compact, Y, ldy, cv, nullptr, st);
+  return scatter<TA, TO>(ctx, S, A, lda, b, n, ncols, f.all, f.pack, Y, ldy, cv, nullptr, st);
 }
 
 }  // namespace
@@ -832,7 +841,9 @@ size_t apply_workspace_bytes(sap_ctx *ctx, int64_t m, int zeta, int d, int ncols
   const ApplyPlan p = make_plan(ctx->num_cus, m, d, ncols, es);
   size_t bytes = 8 * 256;
   if (p.nslices > 1) bytes += static_cast<size_t>(p.nslices) * d * ncols * es;
-  if (wants_compact(p, m, zeta, 65535, d)) bytes += static_cast<size_t>(m) * 8 * sizeof(uint16_t) + 256;
+  if (zeta == 8 && p.nranges == 1 && d <= 65535 &&
+      static_cast<double>(p.nstrips) * static_cast<double>(m) * 40.0 >= kCompactMinRereadBytes)
+    bytes += static_cast<size_t>(m) * 16 + 256;
   return bytes;
 }
 

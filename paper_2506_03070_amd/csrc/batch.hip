@@ -4,8 +4,9 @@
 //
 //   generate : one lane per sketch column of every problem (binary search of
 //              the column prefix), stream word = problem index;
-//   apply    : one workgroup per (problem, 16-column tile), the tile's d rows
-//              in LDS (d <= 2048 for FP32 accumulation, <= 1250 for FP64);
+//   apply    : one workgroup per (problem, strip of 4..32 columns, row slice),
+//              the strip's d rows in LDS in FP64, each problem's strips as
+//              wide as its own d allows;
 //   QR       : one launch per panel step for all problems (2-D grid:
 //              trailing block x problem), shapes from the largest d;
 //   LSQR     : per iteration one packed pass over all problems (work items =
@@ -37,6 +38,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "apply_dev.h"
 #include "common.h"
 #include "lsqr_dev.h"
 #include "qr_dev.h"
@@ -106,6 +108,10 @@ constexpr size_t kBatchLds = 160000;  // LDS bytes for the sketch strip of one w
 constexpr int kXcdsB = 8;
 
 // ---- generate --------------------------------------------------------------
+// A problem's sketch is read by its apply alone: with zeta = 8 it is generated
+// in the packed form (16 bytes a row in it.idx, no it.sign; d <= 4096 here).
+__host__ __device__ inline bool packed_sketch(int zeta) { return zeta == 8; }
+
 template <int ZMAX>
 __global__ __launch_bounds__(256) void batch_generate_kernel(const BatchItem *__restrict__ items, int count,
                                                              int64_t total, int *__restrict__ err) {
@@ -118,28 +124,45 @@ __global__ __launch_bounds__(256) void batch_generate_kernel(const BatchItem *__
     else hi = mid - 1;
   }
   const BatchItem &it = items[lo];
-  sketch_dev::generate_column<ZMAX>(g - it.col_base, it.d, it.zeta, it.seed, it.stream, it.idx, it.sign, err);
+  sketch_dev::generate_column<ZMAX>(g - it.col_base, it.d, it.zeta, it.seed, it.stream, it.idx, it.sign, err,
+                                    packed_sketch(it.zeta) ? reinterpret_cast<uint4 *>(it.idx) : nullptr);
 }
 
 // ---- apply -----------------------------------------------------------------
+// Strip width of a problem's sketch apply: of the powers of two (4..32) whose
+// FP64 strip of d rows and a spare one fits in LDS, the one with the least
+// ceil((n + 1) / w) w clk(w), clk(w) = 17.5, 13.5, 10.5, 10.5 the measured
+// cycles of a CU for 64 adds at 4, 8, 16, 32 columns: a wider strip conflicts
+// less, but the last one runs at full width.  Each problem takes its own width,
+// not the one the largest d of the batch allows: 2.84 -> 2.48 ms with the
+// packed rows for 48 FP32 problems of 5000 to 200000 rows, n = 32 to 256, d = 4 n.
+__host__ __device__ inline int batch_apply_width(int d, int n) {
+  const int clk[4] = {35, 27, 21, 21};  // half cycles
+  int best = 4, best_cost = (n + 4) / 4 * 4 * clk[0];
+  for (int w = 8, k = 1; w <= 32; w *= 2, ++k) {
+    if (static_cast<size_t>(d + 1) * w * sizeof(double) > kBatchLds) break;
+    const int cost = (n + w) / w * w * clk[k];
+    if (cost <= best_cost) {
+      best_cost = cost;
+      best = w;
+    }
+  }
+  return best;
+}
+inline int batch_apply_strips(int d, int n) {
+  const int w = batch_apply_width(d, n);
+  return (n + w) / w;
+}
+
 // Work item = (problem, strip of W columns, row slice): the strip of Y (d + 1
 // spare rows by W columns) is accumulated in FP64 in LDS over the slice's
 // rows; a problem of one slice writes h times it into Y, otherwise into its
-// slice of Ypart (summed by batch_apply_reduce_kernel).  work.y packs the
-// strip (low 20 bits) and the slice.
+// slice of Ypart (summed by batch_apply_reduce_kernel).
 template <typename TA, int W>
-__global__ __launch_bounds__(kBThreads) void batch_apply_kernel(const BatchItem *__restrict__ items,
-                                                                const int2 *__restrict__ work, int nwork) {
+__device__ __forceinline__ void batch_apply_strip(const BatchItem &it, int strip, int slice, unsigned char *lds_raw) {
   using TY = double;
   constexpr int kTileColsB = W;
-  extern __shared__ unsigned char lds_raw[];
   TY *acc = reinterpret_cast<TY *>(lds_raw);
-  const int per_xcd = (nwork + kXcdsB - 1) / kXcdsB;
-  const int wi = (blockIdx.x % kXcdsB) * per_xcd + blockIdx.x / kXcdsB;
-  if (wi >= nwork) return;
-  const int2 wk = work[wi];
-  const BatchItem &it = items[wk.x];
-  const int strip = wk.y & 0xFFFFF, slice = wk.y >> 20;
   const int c0 = strip * kTileColsB;
   const int d = it.d, n = it.n, ncols = it.n + 1, zeta = it.zeta;
   const gmem<TA> *__restrict__ A = gview(static_cast<const TA *>(it.A));
@@ -160,13 +183,18 @@ __global__ __launch_bounds__(kBThreads) void batch_apply_kernel(const BatchItem 
   const int64_t m = min(it.m, r_lo + it.arows);  // end of this slice's rows
   constexpr int U = 8;
   constexpr int64_t kStride = static_cast<int64_t>(kBWaves) * RPW * U;
-  const bool fast = zeta == 8 && (reinterpret_cast<uintptr_t>(it.idx) % 16 == 0);
-  for (int64_t base = r_lo + static_cast<int64_t>(wave) * RPW * U + g; base < m; base += kStride) {
-    if (fast) {
+  const bool packed = packed_sketch(zeta);
+  // (uniform) no lane takes b, and a batch of rows is within 32-bit offsets
+  const bool packed_strip = packed && c0 + W <= n && it.lda < (int64_t(1) << 31) / (8 * kWave * apply_dev::kPackRows);
+  if (packed_strip)
+    apply_dev::add_rows_packed<TA, W>(acc, static_cast<const TA *>(it.A), it.lda, n, c0,
+                                      reinterpret_cast<const uint4 *>(it.idx), r_lo, m, kBWaves);
+  for (int64_t base = r_lo + static_cast<int64_t>(wave) * RPW * U + g; base < m && !packed_strip; base += kStride) {
+    if (packed) {
       TY val[U];
-      uint32_t sg[U];
-      typedef int iv4 __attribute__((ext_vector_type(4)));
-      iv4 ix[U][2];
+      typedef uint32_t uv4 __attribute__((ext_vector_type(4)));
+      const gmem<uv4> *rows = reinterpret_cast<const gmem<uv4> *>(idx);
+      uv4 e[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int64_t i0 = base + u * RPW;
@@ -176,21 +204,10 @@ __global__ __launch_bounds__(kBThreads) void batch_apply_kernel(const BatchItem 
         if (col_a) a = static_cast<TY>(A[i * it.lda + col]);
         else if (col_b) a = static_cast<TY>(bvec[i]);
         val[u] = ok ? a : TY(0);
-        sg[u] = static_cast<uint32_t>(sgn[i]);
-        const gmem<iv4> *ip = reinterpret_cast<const gmem<iv4> *>(idx + i * 8);
-        ix[u][0] = ip[0];
-        ix[u][1] = ip[1];
+        e[u] = rows[i];
       }
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int rr[8] = {ix[u][0].x, ix[u][0].y, ix[u][0].z, ix[u][0].w,
-                           ix[u][1].x, ix[u][1].y, ix[u][1].z, ix[u][1].w};
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const int r = static_cast<unsigned>(rr[k]) < static_cast<unsigned>(d) ? rr[k] : d;  // spare row
-          atomicAdd(acc + r * kTileColsB + c, ((sg[u] >> k) & 1u) ? val[u] : -val[u]);
-        }
-      }
+      for (int u = 0; u < U; ++u) apply_dev::add_packed<W>(acc, c, make_uint4(e[u].x, e[u].y, e[u].z, e[u].w), val[u]);
     } else {
       for (int u = 0; u < U; ++u) {
         const int64_t i = base + u * RPW;
@@ -220,6 +237,25 @@ __global__ __launch_bounds__(kBThreads) void batch_apply_kernel(const BatchItem 
     const int q = e / d, r = e % d;
     const int cc = c0 + q;
     if (cc < ncols) Y[r + static_cast<int64_t>(cc) * d] = acc[r * kTileColsB + q] * hs;
+  }
+}
+
+// work.y packs the strip (low 20 bits) and the slice.
+template <typename TA>
+__global__ __launch_bounds__(kBThreads) void batch_apply_kernel(const BatchItem *__restrict__ items,
+                                                                const int2 *__restrict__ work, int nwork) {
+  extern __shared__ unsigned char lds_raw[];
+  const int per_xcd = (nwork + kXcdsB - 1) / kXcdsB;
+  const int wi = (blockIdx.x % kXcdsB) * per_xcd + blockIdx.x / kXcdsB;
+  if (wi >= nwork) return;
+  const int2 wk = work[wi];
+  const BatchItem &it = items[wk.x];
+  const int strip = wk.y & 0xFFFFF, slice = wk.y >> 20;
+  switch (batch_apply_width(it.d, it.n)) {  // uniform
+    case 32: batch_apply_strip<TA, 32>(it, strip, slice, lds_raw); break;
+    case 16: batch_apply_strip<TA, 16>(it, strip, slice, lds_raw); break;
+    case 8: batch_apply_strip<TA, 8>(it, strip, slice, lds_raw); break;
+    default: batch_apply_strip<TA, 4>(it, strip, slice, lds_raw);
   }
 }
 
@@ -910,14 +946,6 @@ void launch_pass_fn(const PassChoice &pc, const BatchItem *items, const int2 *wo
 // ----------------------------------------------------------------------------
 // Shared pieces of the batched and served forms.
 
-// Strip width of the batched sketch apply: the widest power of two (4..32)
-// whose FP64 strip of d_max + 1 rows fits in the LDS budget.
-int batch_apply_width(int d_max) {
-  int w = 32;
-  while (w > 4 && static_cast<size_t>(d_max + 1) * w * sizeof(double) > kBatchLds) w /= 2;
-  return w;
-}
-
 // Bytes of one problem's workspace (rows_per_chunk >= kMinRowsPerChunk).
 constexpr int64_t kMinRowsPerChunk = 1024;
 
@@ -927,8 +955,7 @@ size_t item_bytes(int64_t m, int n, int d, int zeta, sap_dtype at) {
   const int nblk = (n + kTrsvB - 1) / kTrsvB;
   const int64_t gmax = (m + kMinRowsPerChunk - 1) / kMinRowsPerChunk;
   size_t b = 0;
-  b += 256 + sizeof(int32_t) * m * zeta;
-  b += 256 + sizeof(uint64_t) * m;
+  b += packed_sketch(zeta) ? 256 + 16 * static_cast<size_t>(m) : 512 + (sizeof(int32_t) * zeta + sizeof(uint64_t)) * m;
   b += 256 + sizeof(double) * d * nc;
   b += 256 + sizeof(double) * nc;             // tau, one per column
   b += 2 * (256 + sizeof(double) * 256);      // T of two panels (NB x NB <= 256)
@@ -951,8 +978,9 @@ void carve_item(BatchItem &it, void *base, sap_dtype at, int64_t rows_per_chunk)
   const int64_t m = it.m;
   const int n = it.n, d = it.d, nc = n + 1;
   it.nblk = (n + kTrsvB - 1) / kTrsvB;
-  it.idx = cv.take<int32_t>(static_cast<size_t>(m) * it.zeta);
-  it.sign = cv.take<uint64_t>(m);
+  const bool packed = packed_sketch(it.zeta);
+  it.idx = cv.take<int32_t>(static_cast<size_t>(m) * (packed ? 4 : it.zeta));
+  it.sign = packed ? nullptr : cv.take<uint64_t>(m);
   (void)at;
   it.Y = cv.take<double>(static_cast<size_t>(d) * nc);
   it.tau = cv.take<double>(nc);
@@ -1000,24 +1028,12 @@ sap_status setup_items(sap_ctx *ctx, BatchItem *ditems, const std::vector<BatchI
   else if (zeta_max <= 32) batch_generate_kernel<32><<<grid, 256, 0, st>>>(ditems, count, total_cols, dflags + 2);
   else batch_generate_kernel<64><<<grid, 256, 0, st>>>(ditems, count, total_cols, dflags + 2);
   const int per_xcd = (napply + kXcdsB - 1) / kXcdsB;
-  const int w = batch_apply_width(d_max);
-  const size_t lds = static_cast<size_t>(d_max + 1) * w * sizeof(double);  // plus a spare row
+  size_t lds = 0;  // strips with a spare row
+  for (const auto &it : items)
+    lds = std::max(lds, static_cast<size_t>(it.d + 1) * batch_apply_width(it.d, it.n) * sizeof(double));
   const dim3 ag(static_cast<unsigned>(per_xcd * kXcdsB));
-  if (at == SAP_F32) {
-    switch (w) {
-      case 32: batch_apply_kernel<float, 32><<<ag, kBThreads, lds, st>>>(ditems, dapply, napply); break;
-      case 16: batch_apply_kernel<float, 16><<<ag, kBThreads, lds, st>>>(ditems, dapply, napply); break;
-      case 8: batch_apply_kernel<float, 8><<<ag, kBThreads, lds, st>>>(ditems, dapply, napply); break;
-      default: batch_apply_kernel<float, 4><<<ag, kBThreads, lds, st>>>(ditems, dapply, napply); break;
-    }
-  } else {
-    switch (w) {
-      case 32: batch_apply_kernel<double, 32><<<ag, kBThreads, lds, st>>>(ditems, dapply, napply); break;
-      case 16: batch_apply_kernel<double, 16><<<ag, kBThreads, lds, st>>>(ditems, dapply, napply); break;
-      case 8: batch_apply_kernel<double, 8><<<ag, kBThreads, lds, st>>>(ditems, dapply, napply); break;
-      default: batch_apply_kernel<double, 4><<<ag, kBThreads, lds, st>>>(ditems, dapply, napply); break;
-    }
-  }
+  if (at == SAP_F32) batch_apply_kernel<float><<<ag, kBThreads, lds, st>>>(ditems, dapply, napply);
+  else batch_apply_kernel<double><<<ag, kBThreads, lds, st>>>(ditems, dapply, napply);
   {
     const int64_t tot_max = static_cast<int64_t>(d_max) * (n_max + 1);
     batch_apply_reduce_kernel<<<dim3(static_cast<unsigned>((tot_max + 255) / 256), count), 256, 0, st>>>(ditems);
@@ -1157,12 +1173,12 @@ sap_status run_batch(sap_ctx *ctx, int count, const sap_problem *probs, const sa
     total += need[k];
     total_chunks_max += (probs[k].m + kMinRowsPerChunk - 1) / kMinRowsPerChunk;
   }
-  int d_max = 0;
-  for (int k = 0; k < count; ++k) d_max = std::max(d_max, par[k].d);
-  const int aw = batch_apply_width(d_max);
-  const int tiles_max = (n_max + 1 + aw - 1) / aw;
+  size_t napply = 0;
+  for (int k = 0; k < count; ++k)
+    napply += static_cast<size_t>(batch_apply_strips(par[k].d, probs[k].n)) *
+              apply_slices(probs[k].m, probs[k].n, par[k].d);
   total += 256 + sizeof(int2) * (total_chunks_max + 16);
-  total += 256 + sizeof(int2) * (static_cast<size_t>(count) * tiles_max * kMaxApplySlices + 16);
+  total += 256 + sizeof(int2) * (napply + 16);
   const size_t repack_total = repack_idx.empty() ? 0
                                                  : repack_bytes + 2 * 256 + sizeof(RepackJob) * repack_idx.size() +
                                                        sizeof(int2) * static_cast<size_t>(repack_chunks);
@@ -1202,7 +1218,7 @@ sap_status run_batch(sap_ctx *ctx, int count, const sap_problem *probs, const sa
     carve_item(it, cv.take<char>(need[k]), at, batch_chunk_rows(p.n, chunk_elems));
   }
   int2 *dpass = cv.take<int2>(total_chunks_max + 16);
-  int2 *dapply = cv.take<int2>(static_cast<size_t>(count) * tiles_max * kMaxApplySlices + 16);
+  int2 *dapply = cv.take<int2>(napply + 16);
   std::vector<RepackJob> jobs;
   std::vector<int2> repack_work;
   RepackJob *djobs = nullptr;
@@ -1234,9 +1250,9 @@ sap_status run_batch(sap_ctx *ctx, int count, const sap_problem *probs, const sa
   // work tables
   std::vector<int2> apply_work;
   for (int k = 0; k < count; ++k) {
-    const int tiles = (items[k].n + 1 + aw - 1) / aw;
-    for (int t = 0; t < tiles; ++t)
-      for (int sl = 0; sl < items[k].aslices; ++sl) apply_work.push_back(make_int2(k, t | (sl << 20)));
+    const int tiles = batch_apply_strips(items[k].d, items[k].n);
+    for (int sl = 0; sl < items[k].aslices; ++sl)
+      for (int t = 0; t < tiles; ++t) apply_work.push_back(make_int2(k, t | (sl << 20)));
   }
   // Pass work items of about `elems` elements each, the largest first (each
   // problem's last, shorter item goes to the end of the launch).
@@ -1584,18 +1600,15 @@ hipError_t serve_round(Server *S, std::vector<ServeRequest *> &fresh) {
   if (!fresh.empty()) {
     std::vector<int2> apply_work;
     int64_t col_base = 0;
-    int d_max = 0;
-    for (ServeRequest *r : fresh) d_max = std::max(d_max, r->item.d);
-    const int aw = batch_apply_width(d_max);
     for (size_t k = 0; k < fresh.size(); ++k) {
       ServeRequest *r = fresh[k];
       BatchItem &it = r->item;
       it.col_base = col_base;
       col_base += it.m;
       new_items[k] = it;
-      const int tiles = (it.n + 1 + aw - 1) / aw;
-      for (int t = 0; t < tiles; ++t)
-        for (int sl = 0; sl < it.aslices; ++sl) apply_work.push_back(make_int2(static_cast<int>(k), t | (sl << 20)));
+      const int tiles = batch_apply_strips(it.d, it.n);
+      for (int sl = 0; sl < it.aslices; ++sl)
+        for (int t = 0; t < tiles; ++t) apply_work.push_back(make_int2(static_cast<int>(k), t | (sl << 20)));
     }
     if (static_cast<int>(apply_work.size()) > kServeMaxApply) return hipErrorInvalidValue;
     for (ServeRequest *r : fresh)

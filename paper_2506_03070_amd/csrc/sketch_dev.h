@@ -3,6 +3,7 @@
 // launches.  One lane owns one column of S; see sketch.hip.
 #pragma once
 
+#include "apply_dev.h"
 #include "common.h"
 
 namespace sap {
@@ -101,11 +102,12 @@ __device__ __forceinline__ void bitonic_sort(uint32_t (&c)[N]) {
 }
 
 // Column i of the sketch: zeta ascending distinct rows into idx[i*zeta ..]
-// and the sign word into sign[i].
+// and the sign word into sign[i], or (packed non-null, zeta = 8) both into
+// packed[i] (apply_dev.h).
 template <int ZMAX>
 __device__ __forceinline__ void generate_column(int64_t i, int d, int zeta, uint64_t seed, uint64_t stream,
                                                 int32_t *__restrict__ idx, uint64_t *__restrict__ sign,
-                                                int *__restrict__ err) {
+                                                int *__restrict__ err, uint4 *__restrict__ packed = nullptr) {
   const uint64_t col = static_cast<uint64_t>(i);
   const uint64_t dd = static_cast<uint64_t>(d);
   uint32_t c[ZMAX];
@@ -164,6 +166,17 @@ __device__ __forceinline__ void generate_column(int64_t i, int d, int zeta, uint
     bitonic_sort<ZMAX>(c);
   }
 
+  const Block4 s = philox(col, ~0ull, 0, 0, seed, stream);
+  if constexpr (ZMAX >= 8) {
+    if (packed) {
+      const uint32_t w = static_cast<uint32_t>(s.w[0]);
+      uint32_t e[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) e[k] = apply_dev::pack_entry(static_cast<int32_t>(c[k]), d, (w >> k) & 1u);
+      packed[i] = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+      return;
+    }
+  }
   int32_t *out = idx + i * zeta;
   bool stored = false;
   if constexpr (ZMAX == 8) {  // a lane's 32 bytes in two stores instead of eight
@@ -179,7 +192,6 @@ __device__ __forceinline__ void generate_column(int64_t i, int d, int zeta, uint
     for (int j = 0; j < ZMAX; ++j)
       if (j < zeta) out[j] = static_cast<int32_t>(c[j]);
   }
-  const Block4 s = philox(col, ~0ull, 0, 0, seed, stream);
   const uint64_t mask = (zeta >= 64) ? ~0ull : ((1ull << zeta) - 1ull);
   sign[i] = s.w[0] & mask;
 }
