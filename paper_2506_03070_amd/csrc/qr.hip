@@ -19,12 +19,14 @@
 // before it, so the chain completes whatever number of them is resident.
 //
 // What bounds it: the dependent chain from panel to panel (not the flops: 4%
-// of the FP64 peak at 4000 x 1001).  Per 4-column panel at 4000 rows 8.5 us:
-// flag seen 0.8, reflectors in 1.3, V^T C 1.5, W2 0.4, the panel's 4
-// reflectors 1.6, update and new rows 0.8, rows out and acknowledged 2.4 (16.0
-// us with one workgroup reduction per column and selects on every row: apply
-// 6.7, factor 6.5).  4000 x 1001: 3.95 -> 2.12 ms, 1026 x 257: 0.75 -> 0.40,
-// 400 x 101: 0.23 -> 0.12, 8000 x 1001: 6.65 -> 5.0.
+// of the FP64 peak at 4000 x 1001).  Per 4-column panel at 4000 rows 8.2 us:
+// V^T C 1.5, W2 0.4, the panel's 4 reflectors 1.6, update and new rows 0.8, the
+// rest the rows' way out of one CU and into the next (128 KB; 4.5 us when the
+// next block waited for the flag, see kDirect below).  16.0 us with one
+// workgroup reduction per column and selects on every row: apply 6.7, factor
+// 6.5.  4000 x 1001: 3.95 -> 2.05 ms (2.14 by flags), 2000 x 501: 1.49 -> 0.75
+// (0.80), 1026 x 257: 0.75 -> 0.37 (0.40), 1000 x 251: 0.64 -> 0.30 (0.33),
+// 400 x 101: 0.23 -> 0.11 (0.12), 8000 x 1001: 6.65 -> 4.9 (5.0).
 // Sketches taller than 4096 rows and wider than 192 columns take the
 // two-level form below: 64-column panels factored by the chained form, the
 // trailing matrix updated on the FP64 matrix cores.
@@ -50,6 +52,56 @@ constexpr int kQrSpinLimit = 1 << 20;
 // last one arrives.
 constexpr int kWarm = 3;
 
+// The hand-over from a block to the kDirect next ones, which the chain waits
+// for, goes without its flag: the block, once its columns are in registers,
+// marks their places in memory (and T's) with kHole and says so (flag 1), and
+// those blocks then read the reflectors' places themselves until no hole is
+// left, each wave its own rows.  The rows' acknowledgement, the flag's way and
+// a second trip for the rows leave the chain that way; blocks further behind
+// wait for flag 2.  A hole is a signalling NaN, which no arithmetic returns, and
+// the columns are quieted as they are loaded, so a published value is never a
+// hole.  The first kDirectFrom blocks have no time to mark their places.  Three
+// blocks: the block after next has to be ready when the next one publishes
+// (1026 x 257: 379 us with two, 372 with three, 369 with four, 373 with eight;
+// 8000 x 64: 214, 218, 221, 223, the readers' traffic).
+constexpr int kDirect = 3;
+constexpr int kDirectFrom = 4;
+constexpr int kHoleHi = 0x7FF4D15C;
+__device__ __forceinline__ bool is_hole(double v) { return __double2hiint(v) == kHoleHi; }
+
+// Panel columns as load_columns<kCoherent> gives them and T's element, read
+// until they hold no hole (or the polls run out: the NaN then spreads to the
+// block).  Only what had a hole is read again.
+template <int S, int NB, int TH>
+__device__ __forceinline__ void load_published(const double *base, int64_t ldy, int rows, int lo, const double *Tel,
+                                               double (&V)[S][NB], double &tel) {
+  static_assert(S * NB <= 32, "one bit a register");
+  __amdgpu_buffer_rsrc_t col[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) col[i] = column_buffer(base + static_cast<int64_t>(i) * ldy, rows);
+  load_columns<S, NB, TH, kCoherent>(base, ldy, rows, NB, lo, V);
+  tel = load_coherent(Tel);
+  for (int spins = 0; spins < kQrSpinLimit; ++spins) {
+    unsigned holes = 0;
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int i = 0; i < NB; ++i) holes |= __any(is_hole(V[s][i])) ? 1u << (s * NB + i) : 0u;
+    const bool t_hole = __any(is_hole(tel));
+    if (holes == 0 && !t_hole) return;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const int r = static_cast<int>(threadIdx.x) + TH * s;
+      int off = r >= lo ? r * 8 : kNoRow;
+      asm volatile("" : "+v"(off));  // a read of its own, not the earlier one's value
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+        if ((holes >> (s * NB + i)) & 1u) V[s][i] = load_row<kCoherent>(col[i], off);  // uniform
+    }
+    if (t_hole) tel = load_coherent(Tel);
+  }
+}
+
 // One launch of ceil(cols / NB) workgroups; w: the ticket word and one flag
 // per panel, zero on entry; Tall: NB x NB per panel.
 template <int S, int NB, int TH>
@@ -71,21 +123,40 @@ __global__ __launch_bounds__(TH) void qr_chain_kernel(double *__restrict__ Y, in
   double *base = Y + static_cast<int64_t>(c0) * ldy;
   double C[S][NB];
   load_columns<S, NB, TH, 0>(base, ldy, d, ncb, 0, C);
+#pragma unroll
+  for (int s = 0; s < S; ++s)
+#pragma unroll
+    for (int c = 0; c < NB; ++c) C[s][c] = __builtin_canonicalize(C[s][c]);
+  if (j >= kDirectFrom) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the columns are read
+    double H[S][NB];
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int c = 0; c < NB; ++c) H[s][c] = __hiloint2double(kHoleHi, 0);
+    store_columns<S, NB, TH, kCoherent>(base, ldy, d, ncb, c0, H);
+    if (t < NB * NB) store_coherent(Tall + j * NB * NB + t, __hiloint2double(kHoleHi, 0));
+    publish_flag(flags + j, 1);
+  }
+  const auto wait_flag_at = [&](int k, int value) {  // by one thread
+    int spins = 0;
+    while (__hip_atomic_load(flags + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < value) {
+      __builtin_amdgcn_s_sleep(1);
+      if (++spins > kQrSpinLimit) {
+        failed = 1;
+        break;
+      }
+    }
+  };
+  const int direct = max(j - kDirect, kDirectFrom);  // panels from here on come without their flag
+  if (t == 0)
+    for (int k = direct; k < j; ++k) wait_flag_at(k, 1);
   const auto store_t = [&](int e, double v) { store_coherent(Tall + j * NB * NB + e, v); };
   if (j <= kWarm) gram_prepare<S, NB, TH>(C, sh, min(j, 1) * NB);
   bool expired = false;
   // the first block (j = 0) makes one round without reflectors, k = -1
   for (int k = min(j, 1) - 1; k < j; ++k) {
-    if (t == 0 && k >= 0) {
-      int spins = 0;
-      while (__hip_atomic_load(flags + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < 1) {
-        __builtin_amdgcn_s_sleep(1);
-        if (++spins > kQrSpinLimit) {
-          failed = 1;
-          break;
-        }
-      }
-    }
+    if (t == 0 && k >= 0 && k < direct) wait_flag_at(k, 2);
     __syncthreads();
     expired = __builtin_amdgcn_readfirstlane(failed) != 0;
     if (expired) break;
@@ -93,9 +164,15 @@ __global__ __launch_bounds__(TH) void qr_chain_kernel(double *__restrict__ Y, in
     // threads hold, and T (element e in lane e of every wave), through the
     // coherence point: another workgroup wrote them during this launch.
     const int k0 = k * NB;
-    const double tel = k < 0 ? 0.0 : load_coherent(Tall + k * NB * NB + (t & (kWave - 1)) % (NB * NB));
-    double V[S][NB];
-    load_columns<S, NB, TH, kCoherent>(Y + static_cast<int64_t>(max(k0, 0)) * ldy, ldy, k < 0 ? 0 : d, NB, k0, V);
+    const double *Vk = Y + static_cast<int64_t>(max(k0, 0)) * ldy;
+    const double *Tel = Tall + max(k, 0) * NB * NB + (t & (kWave - 1)) % (NB * NB);
+    double V[S][NB], tel = 0.0;
+    if (k >= direct) {
+      load_published<S, NB, TH>(Vk, ldy, d, k0, Tel, V, tel);
+    } else {
+      if (k >= 0) tel = load_coherent(Tel);
+      load_columns<S, NB, TH, kCoherent>(Vk, ldy, k < 0 ? 0 : d, NB, k0, V);
+    }
     unit_lower<S, NB, TH>(V, k0);
     const auto put_r = [&](int r, int x, double v) {
       if (x < ncb) base[k0 + r + static_cast<int64_t>(x) * ldy] = v;
@@ -112,7 +189,7 @@ __global__ __launch_bounds__(TH) void qr_chain_kernel(double *__restrict__ Y, in
       for (int c = 0; c < NB; ++c) C[s][c] = __builtin_nan("");
   }
   store_columns<S, NB, TH, kCoherent>(base, ldy, d, ncb, c0, C);
-  publish_flag(flags + j, 1);
+  publish_flag(flags + j, 2);
 }
 
 __global__ void qr_chain_zero_kernel(int *w, int count) {
