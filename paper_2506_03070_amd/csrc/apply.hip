@@ -540,11 +540,14 @@ ApplyPlan make_plan(int num_cus, int64_t m, int d, int ncols, size_t esize) {
 
 // Time estimates (us) that the choices below compare; measured on one MI355X.
 // Cycles of a CU for 64 adds in the scatter form, loads and bank conflicts
-// included, with packed rows: 10.5 for W = 32 and 16, 13.5, 18.5 (d = 4000), 25
-// (8000), 33 (12000) for W = 1; 3 more from the 32-bit indices, half as much
-// again on the general path (zeta != 8).
-double scatter_us(int num_cus, int zeta, const ApplyPlan &p, bool pack) {
-  const double clk = ((p.w >= 16 ? 10.5 : p.w == 8 ? 13.5 : p.w == 4 ? 18.5 : p.w == 2 ? 25 : 33) *
+// included, with packed rows: 10.5 for W = 32 and 16, 13.5, 18.5 (d = 4000); for
+// W = 2 (d = 8000) and 1 (12000) 25 and 33 while A stays in the 256 MB cache
+// behind the XCDs (20000 rows of 1000 FP64) and 31 and 49 beyond (2^18 rows),
+// where a 128-byte line moves for each 16 or 8 bytes; 3 more from the 32-bit
+// indices, half as much again on the general path (zeta != 8).
+double scatter_us(int num_cus, int zeta, const ApplyPlan &p, bool pack, bool near) {
+  const double clk = ((p.w >= 16 ? 10.5 : p.w == 8 ? 13.5 : p.w == 4 ? 18.5 : p.w == 2 ? (near ? 25 : 31)
+                                                                                       : (near ? 33 : 49)) *
                           (zeta == 8 && p.nranges == 1 ? 1.0 : 1.5) +
                       (pack ? 0 : 3)) *
                      p.nranges;
@@ -565,15 +568,16 @@ double parts_us(int nslices, int d, int ncols, size_t es) {
 // items on 256 CUs take as long as 512 (300007 x 513, d = 2052), and 4 strips of
 // 20000 rows in slices of 4096 keep 16 CUs busy (20000 x 100, d = 400: 114 us,
 // 33 in slices of 512).
-ApplyPlan fine_plan(int num_cus, int64_t m, int zeta, int d, int ncols, size_t es, const ApplyPlan &p, bool pack) {
+ApplyPlan fine_plan(int num_cus, int64_t m, int zeta, int d, int ncols, size_t es, const ApplyPlan &p, bool pack,
+                    bool near) {
   ApplyPlan best = p;
-  double best_us = scatter_us(num_cus, zeta, p, pack) + parts_us(p.nslices, d, ncols, es);
+  double best_us = scatter_us(num_cus, zeta, p, pack, near) + parts_us(p.nslices, d, ncols, es);
   const int most = static_cast<int>(std::min<int64_t>(64, (m + kFineSliceRows - 1) / kFineSliceRows));
   for (int ns = 1; ns <= most; ++ns) {
     ApplyPlan q = p;
     q.rows_per_slice = (m + ns - 1) / ns;
     q.nslices = static_cast<int>((m + q.rows_per_slice - 1) / q.rows_per_slice);
-    const double us = scatter_us(num_cus, zeta, q, pack) + parts_us(q.nslices, d, ncols, es);
+    const double us = scatter_us(num_cus, zeta, q, pack, near) + parts_us(q.nslices, d, ncols, es);
     if (us < 0.98 * best_us) {
       best_us = us;
       best = q;
@@ -667,13 +671,14 @@ FullPlan full_plan(int num_cus, int64_t m, int zeta, int d, int n, int64_t lda, 
   const int ncols = n + (with_b ? 1 : 0);
   const ApplyPlan p = make_plan(num_cus, m, d, ncols, sizeof(double));
   f.pack = wants_pack(num_cus, m, zeta, d, lda, p);
-  f.all = fine_plan(num_cus, m, zeta, d, ncols, es, p, f.pack);
+  const bool near = static_cast<double>(m) * lda * (a_type == SAP_F64 ? 8 : a_type == SAP_F32 ? 4 : 2) <= 256e6;
+  f.all = fine_plan(num_cus, m, zeta, d, ncols, es, p, f.pack, near);
   const size_t copy = f.pack ? static_cast<size_t>(m) * 16 + 256 : 0;
   f.scatter_bytes = part_bytes(f.all.nslices, d, ncols, es) + copy + 1024;
   f.a = make_plan(num_cus, m, d, n, sizeof(double));
-  f.b = fine_plan(num_cus, m, zeta, d, 1, es, make_plan(num_cus, m, d, 1, sizeof(double)), false);
+  f.b = fine_plan(num_cus, m, zeta, d, 1, es, make_plan(num_cus, m, d, 1, sizeof(double)), false, true);
   f.g = make_gather(num_cus, m, zeta, d, n, lda, a_type, es,
-                    scatter_us(num_cus, zeta, f.all, f.pack) + parts_us(f.all.nslices, d, ncols, es));
+                    scatter_us(num_cus, zeta, f.all, f.pack, near) + parts_us(f.all.nslices, d, ncols, es));
   f.gather_bytes = f.g.use ? f.g.bytes + part_bytes(f.a.nslices, d, n, es) + copy +
                                  (with_b ? part_bytes(f.b.nslices, d, 1, es) : 0) + 2048
                            : 0;
