@@ -932,7 +932,7 @@ def main():
                      "achieved": pass_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": pass_gbs / HBM_PEAK_GBS,
                      "traffic": measured_traffic(m, n), "bytes_per_launch": pb, "avg_launch_ms": pass_avg_ms,
                      "launches": n_pass, "full_launches": n_full},
-        "sa": {"kernel": "apply_strip_kernel", "achieved_gbs": apply_gbs, "frac": apply_gbs / HBM_PEAK_GBS,
+        "sa": {"kernel": "sps_apply (apply_gather_kernel here)", "achieved_gbs": apply_gbs, "frac": apply_gbs / HBM_PEAK_GBS,
                "bytes_per_launch": ab, "avg_launch_ms": apply_avg_ms, "launches": n_apply,
                "a_only_gbs": m * n * 8 / (apply_avg_ms * 1e-3) / 1e9},
         "qr": {"flops": qr_flops(d, n + 1), "ms": med("t_qr_ms"),

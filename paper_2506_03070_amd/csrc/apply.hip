@@ -14,8 +14,9 @@
 //     row (same address for the W lanes: one broadcast);
 //   * only when even W = 1 does not fit (d >= 20000) are the rows of Y split
 //     into ranges, each range skipping the nonzeros outside it.
-// It is bound by the LDS adds: 9.5 cycles a wave instruction for W = 32, 17 at
-// W = 4 (bank conflicts between the rows of an instruction), more below.
+// It is bound by the LDS adds: 9.5 cycles a wave instruction without conflicts,
+// 10.5 as run at W = 32, 18.5 at W = 4 (bank conflicts between the rows of an
+// instruction), more below, where the lines of A count as well.
 //
 // Gather (apply_lists_kernel, apply_gather_kernel).  The strip (4 columns, or 2
 // above 8192 rows) sits in registers, thread t holding rows t, t + 1024, ...;
@@ -361,10 +362,12 @@ struct Piece {
 // while the next tile's loads go out one by one between the chunks: loads
 // return in order, so a list asked for behind a whole tile would wait for all
 // of it (that cost 1.65 ms of 4.3 at 2^20 x 1000, d = 4000).  Lists run three
-// chunks ahead.  Bound by the LDS reads (8.5 cycles a 16-byte wave read, half of
-// them bank conflicts) and the vector work of an entry (10 instructions for 4
-// columns); lists are about twice as long as their entries, since the 64 rows
-// of a group wait for the longest.
+// chunks ahead.  Bound by the lines that move from L2: a row's 16- or 32-byte
+// piece takes a 128-byte line (2^19 x 1000 FP64: 1.3e8 requests, 17 GB; 1.77 ms,
+// 1.18 without the tile loads).  The LDS reads (8.5 cycles a 16-byte wave read,
+// half of them bank conflicts) and the vector work (10 instructions an entry of 4
+// columns) come next; lists are about twice as long as their entries, since the
+// 64 rows of a group wait for the longest.
 template <typename TA, typename TO, int S, int W>
 __global__ __launch_bounds__(kApplyThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void apply_gather_kernel(
     const uint32_t *__restrict__ off, const uint2 *__restrict__ lists, const int *__restrict__ flag,
@@ -839,7 +842,7 @@ sap_status apply_scratch_init(sap_ctx *ctx) {
 }
 
 // What every apply is given at least (and the size a caller's limits are held
-// against): the scatter form's partial strips and 16-bit copy.  An FP32 Y's
+// against): the scatter form's partial strips and packed copy.  An FP32 Y's
 // FP64 sums make narrower strips and so never more slices than counted here.
 size_t apply_workspace_bytes(sap_ctx *ctx, int64_t m, int zeta, int d, int ncols, sap_dtype y_type) {
   const size_t es = (y_type == SAP_F64) ? 8 : 4;

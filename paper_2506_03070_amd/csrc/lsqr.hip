@@ -1368,7 +1368,7 @@ sap_status run_lsqr(sap_ctx *ctx, const sap_problem *prob, const double *R, int6
       }
       if (hs.total_iters >= maxiter) break;
     }
-    // Iterations in batches; one state read per batch.  The update kernel
+    // Iterations in batches; one state read per batch.  lsqr_mv_kernel
     // sets `done` no later than iteration maxiter, so the batch count is
     // bounded.
     const int max_batches = maxiter / batch + 2;
