@@ -287,6 +287,7 @@ __global__ __launch_bounds__(kPanelThreads) void batch_qr_first_kernel(const Bat
     for (int i = 0; i < NB; ++i) V[s][i] = 0.0;
   gram_prepare<S, NB, kPanelThreads>(P, sh, 0);
   __syncthreads();
+  if (threadIdx.x < kWave) gram_total<NB, kPanelThreads>(sh);
   factor_update<S, NB, kPanelThreads>(
       P, V, 0.0, sh, nb, rows, 0, 0, it.tau, true, true, [](int, int, double) {}, [&](int e, double v) { it.T0[e] = v; });
   store_columns<S, NB, kPanelThreads, 0>(it.Y, rows, rows, nb, 0, P);
@@ -316,6 +317,7 @@ __global__ __launch_bounds__(kPanelThreads) void batch_qr_step_kernel(const Batc
   unit_lower<S, NB, kPanelThreads>(V, 0);
   if (blockIdx.x == 0) {
     __syncthreads();
+    if (threadIdx.x < kWave) gram_total<NB, kPanelThreads>(sh);
     factor_update<S, NB, kPanelThreads>(
         C, V, tel, sh, ncb, dr, NB, c0, it.tau, true, true,
         [&](int r, int x, double v) {

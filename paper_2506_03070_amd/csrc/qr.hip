@@ -24,9 +24,10 @@
 // rest the rows' way out of one CU and into the next (128 KB; 4.5 us when the
 // next block waited for the flag, see kDirect below).  16.0 us with one
 // workgroup reduction per column and selects on every row: apply 6.7, factor
-// 6.5.  4000 x 1001: 3.95 -> 2.05 ms (2.14 by flags), 2000 x 501: 1.49 -> 0.75
-// (0.80), 1026 x 257: 0.75 -> 0.37 (0.40), 1000 x 251: 0.64 -> 0.30 (0.33),
-// 400 x 101: 0.23 -> 0.11 (0.12), 8000 x 1001: 6.65 -> 4.9 (5.0).
+// 6.5.  4000 x 1001: 3.96 -> 2.10 ms, 2000 x 501: 1.50 -> 0.79, 1026 x 257: 0.75 ->
+// 0.40, 400 x 101: 0.245 -> 0.128, 8000 x 1001: 6.67 -> 5.10, 64 x 33 (mostly column
+// by column): 0.090 -> 0.087.  2 to 5% of that goes into the Gram form's exactness
+// (factor_update in qr_dev.h): 2.05, 0.75, 0.38, 0.122, 4.92, 0.052 without.
 // Sketches taller than 4096 rows and wider than 192 columns take the
 // two-level form below: 64-column panels factored by the chained form, the
 // trailing matrix updated on the FP64 matrix cores.
@@ -160,6 +161,8 @@ __global__ __launch_bounds__(TH) void qr_chain_kernel(double *__restrict__ Y, in
     __syncthreads();
     expired = __builtin_amdgcn_readfirstlane(failed) != 0;
     if (expired) break;
+    const bool last = k == j - 1, warm = k >= j - kWarm;
+    if (warm && t < kWave) gram_total<NB, TH>(sh);
     // Panel k's reflectors (a full panel: k < j) at the rows this block's
     // threads hold, and T (element e in lane e of every wave), through the
     // coherence point: another workgroup wrote them during this launch.
@@ -177,7 +180,6 @@ __global__ __launch_bounds__(TH) void qr_chain_kernel(double *__restrict__ Y, in
     const auto put_r = [&](int r, int x, double v) {
       if (x < ncb) base[k0 + r + static_cast<int64_t>(x) * ldy] = v;
     };
-    const bool last = k == j - 1, warm = k >= j - kWarm;
     factor_update<S, NB, TH>(C, V, tel, sh, ncb, d, k0 + NB, c0, tau, warm, last, put_r, store_t);
     // G while the next panel is still on its way
     if (warm && !last) gram_prepare<S, NB, TH>(C, sh, k0 + 2 * NB);
