@@ -127,42 +127,26 @@ __device__ __forceinline__ void chain_block(const double *__restrict__ M, int64_
 }
 
 // Inverse of diagonal block b of R (upper) and its transpose (for R^T); 256
-// threads.  The block's four 16 x 16 diagonal blocks are inverted at once, one
-// a wave (a lane a column, back substitution in registers), then joined twice
-// by X12 = -X11 (R12 X22).  One thread a column over the whole block is a
-// chain of 2016 dependent LDS products (49 us; this form 17).
+// threads.  A column of the inverse is the back substitution of R_bb x = e_c, by
+// blocks of 16 rows: the four 16 x 16 diagonal blocks at once, one a wave (a lane
+// a column, in registers), then the blocks above them one diagonal after the other,
+// again one a wave: the rows below summed by all lanes, the 16 x 16 triangle solved
+// by a lane a column.  (Blocks joined by products with inverses, X12 = -X11 (R12
+// X22), are not back substitution: sap_trsv at n = 64 then was 1.4 to 1.6 times as
+// far off on the R of sketches with singular values 1 to 1e-10.)
+// One thread a column over the whole block is a chain of 2016 dependent LDS
+// products (49 us; this form 21, joined blocks 15).
+constexpr int kTrsvQ = kTrsvB / 4;
 struct TrsvPrepShared {
   double Rb[kTrsvB][kTrsvB + 1];
   double X[kTrsvB][kTrsvB + 1];  // X[row][col] = (R_bb^-1)(row, col)
-  double T[kTrsvB / 2][kTrsvB / 2 + 1];
+  double T[3 * kTrsvQ][kTrsvQ + 1];
 };
-
-// X12 = -X11 (R12 X22) for the blocks of H rows at o and o + H, by `threads`
-// threads (t of them), T: their H x H scratch.  Two barriers, taken by all.
-template <int H>
-__device__ __forceinline__ void trsv_join(TrsvPrepShared &sh, int o, int t, int threads, int trow) {
-  for (int e = t; e < H * H; e += threads) {
-    const int r = e / H, c = e % H;
-    double s = 0.0;
-#pragma unroll 8
-    for (int k = 0; k < H; ++k) s += sh.Rb[o + r][o + H + k] * sh.X[o + H + k][o + H + c];
-    sh.T[trow + r][c] = s;
-  }
-  __syncthreads();
-  for (int e = t; e < H * H; e += threads) {
-    const int r = e / H, c = e % H;
-    double s = 0.0;
-#pragma unroll 8
-    for (int k = 0; k < H; ++k) s += sh.X[o + r][o + k] * sh.T[trow + k][c];
-    sh.X[o + r][o + H + c] = -s;
-  }
-  __syncthreads();
-}
 
 __device__ __forceinline__ void trsv_invert_diag_block(const double *__restrict__ R, int64_t ldr, int n, int b,
                                                        double *__restrict__ Dup, double *__restrict__ Dlo,
                                                        TrsvPrepShared &sh) {
-  constexpr int Q = kTrsvB / 4;
+  constexpr int Q = kTrsvQ;
   const int t = threadIdx.x;
   const int k0 = b * kTrsvB;
   const int kn = min(kTrsvB, n - k0);
@@ -172,22 +156,46 @@ __device__ __forceinline__ void trsv_invert_diag_block(const double *__restrict_
     sh.X[rr][cc] = 0.0;
   }
   __syncthreads();
-  const int o = Q * (t / kWave), c = t % kWave;
-  if (c < Q) {
+  const int i = t / kWave, c = t % kWave, o = Q * i;
+  if (c < Q && o + c < kn) {  // columns past the matrix's end stay zero
     double x[Q];
 #pragma unroll
     for (int rr = Q - 1; rr >= 0; --rr) {
       double s = rr == c ? 1.0 : 0.0;
 #pragma unroll
       for (int k = rr + 1; k < Q; ++k) s -= sh.Rb[o + rr][o + k] * x[k];
-      // rows past the matrix's end stay zero, as do rows below the diagonal
-      x[rr] = (rr <= c && o + c < kn) ? s / sh.Rb[o + rr][o + rr] : 0.0;
+      x[rr] = rr <= c ? s / sh.Rb[o + rr][o + rr] : 0.0;  // rows below the diagonal stay zero
       sh.X[o + rr][o + c] = x[rr];
     }
   }
   __syncthreads();
-  trsv_join<Q>(sh, 2 * Q * (t / (2 * kWave)), t % (2 * kWave), 2 * kWave, Q * (t / (2 * kWave)));
-  trsv_join<2 * Q>(sh, 0, t, 4 * kWave, 0);
+#pragma unroll
+  for (int dg = 1; dg < 4; ++dg) {
+    const int oc = o + Q * dg;  // block (rows o .., columns oc ..)
+    if (i + dg < 4) {           // uniform
+      for (int e = c; e < Q * Q; e += kWave) {
+        const int rr = e / Q, cc = e % Q;
+        double s = 0.0;
+#pragma unroll 8
+        for (int k = Q; k < Q * (dg + 1); ++k) s += sh.Rb[o + rr][o + k] * sh.X[o + k][oc + cc];
+        sh.T[o + rr][cc] = s;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      __builtin_amdgcn_wave_barrier();
+      if (c < Q && oc + c < kn) {
+        double x[Q];
+#pragma unroll
+        for (int rr = Q - 1; rr >= 0; --rr) {
+          double s = -sh.T[o + rr][c];
+#pragma unroll
+          for (int k = rr + 1; k < Q; ++k) s -= sh.Rb[o + rr][o + k] * x[k];
+          x[rr] = s / sh.Rb[o + rr][o + rr];
+          sh.X[o + rr][oc + c] = x[rr];
+        }
+      }
+    }
+    __syncthreads();
+  }
   double *du = Dup + static_cast<int64_t>(b) * kTrsvB * kTrsvB;
   double *dl = Dlo + static_cast<int64_t>(b) * kTrsvB * kTrsvB;
   for (int e = t; e < kTrsvB * kTrsvB; e += blockDim.x) {
