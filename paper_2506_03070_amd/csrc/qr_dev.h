@@ -711,7 +711,8 @@ __device__ __forceinline__ void factor_small(PanelShared<NB, TH> &sh, int nb, do
 // 1 to 1e-6) 1.1, 1.6, 1.4 against 1.00.
 //
 // warm = false is the update alone; warm without last runs the factorisation's
-// code too, with U the identity and nothing stored.
+// code too, with U the identity (left out for a panel that would be refused) and
+// nothing stored.
 template <int S, int NB, int TH, typename PutR, typename StoreT>
 __device__ __forceinline__ void factor_update(double (&C)[S][NB], const double (&V)[S][NB], double tel,
                                               PanelShared<NB, TH> &sh, int nb, int hi, int roff, int k0,
@@ -739,7 +740,9 @@ __device__ __forceinline__ void factor_update(double (&C)[S][NB], const double (
   __builtin_amdgcn_sched_barrier(0);
   double W2[NB][NB];
   spread_w2<NB>(w2, W2);
-  const bool slow = last && (hi - roff < 4 * NB || __builtin_amdgcn_readfirstlane(sh.slow) != 0);
+  // refused (a round that is not the last then leaves the panel as it is: the
+  // identity would carry a non-finite column into the ones to its right)
+  const bool slow = warm && (hi - roff < 4 * NB || __builtin_amdgcn_readfirstlane(sh.slow) != 0);
 #pragma unroll
   for (int s = 0; s < S; ++s) update_row<NB>(C[s], V[s], W2);
   if (roff >= NB)
@@ -766,7 +769,7 @@ __device__ __forceinline__ void factor_update(double (&C)[S][NB], const double (
         C[s][x] = q;
       }
   }
-  if (slow) {
+  if (last && slow) {
     __syncthreads();  // earlier users of the shared buffers are done
     factor_panel_columns<S, NB, TH>(C, sh, nb, hi - roff, roff, k0, tau);
   } else if (last) {
