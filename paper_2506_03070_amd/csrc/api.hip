@@ -31,6 +31,17 @@ sap_status hip_fail(sap_ctx *ctx, hipError_t e, const char *what) {
   return fail(ctx, SAP_EDEVICE, msg);
 }
 
+bool HipMem::alloc(void **p, size_t bytes) {
+  if (hipMalloc(p, bytes) == hipSuccess) return true;
+  (void)hipGetLastError();
+  return false;
+}
+void HipMem::free(void *p) { (void)hipFree(p); }
+size_t HipMem::available() {
+  size_t free_b = 0, total_b = 0;
+  return hipMemGetInfo(&free_b, &total_b) == hipSuccess ? free_b : 0;
+}
+
 sap_status ensure_workspace(sap_ctx *ctx, size_t bytes, hipStream_t stream) {
   bytes = (bytes + 4095) & ~size_t(4095);
   if (bytes <= ctx->ws_size) return SAP_OK;
@@ -43,20 +54,27 @@ sap_status ensure_workspace(sap_ctx *ctx, size_t bytes, hipStream_t stream) {
     ctx->ws = nullptr;
     ctx->ws_size = 0;
   }
-  if (hipMalloc(&ctx->ws, bytes) != hipSuccess) {
-    (void)hipGetLastError();
-    ctx->ws = nullptr;
-    return fail(ctx, SAP_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
+  if (bytes + ctx->apply_opt.size > ctx->budget) ctx->apply_opt.release(ctx->apply_mem);
+  if (!ctx->apply_mem.alloc(&ctx->ws, bytes)) {
+    ctx->apply_opt.release(ctx->apply_mem);
+    if (!ctx->apply_mem.alloc(&ctx->ws, bytes)) {
+      ctx->ws = nullptr;
+      return fail(ctx, SAP_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
+    }
   }
   ctx->ws_size = bytes;
   return SAP_OK;
 }
 
-sap_status ensure_workspace_upto(sap_ctx *ctx, size_t needed, size_t wanted, size_t *got, hipStream_t stream) {
-  *got = wanted;
-  if (wanted > needed && ensure_workspace(ctx, wanted, stream) == SAP_OK) return SAP_OK;
-  *got = needed;
-  return ensure_workspace(ctx, needed, stream);
+sap_status launch_apply_optional(sap_ctx *ctx, const sps_sketch *S, const void *A, int64_t lda, sap_dtype a_type,
+                                 const double *b, int n, void *Y, int64_t ldy, sap_dtype y_type, void *work,
+                                 size_t work_bytes, hipStream_t st) {
+  const size_t wanted = apply_workspace_wanted(ctx, S->m, S->zeta, S->d, n, lda, b != nullptr, a_type, y_type);
+  if (wanted > work_bytes && ctx->apply_opt.reserve(ctx->apply_mem, wanted, ctx->budget - ctx->ws_size)) {
+    work = ctx->apply_opt.base;
+    work_bytes = ctx->apply_opt.size;
+  }
+  return launch_apply(ctx, S, A, lda, a_type, b, n, Y, ldy, y_type, work, work_bytes, st);
 }
 
 static hipEvent_t take_event(sap_ctx *ctx) {
@@ -223,6 +241,7 @@ void sap_destroy(sap_ctx *ctx) {
     if (e) (void)hipEventDestroy(e);
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
   if (ctx->ws) (void)hipFree(ctx->ws);
+  ctx->apply_opt.release(ctx->apply_mem);
   delete ctx;
 }
 
@@ -276,13 +295,12 @@ sap_status sps_apply(sap_ctx *ctx, const sps_sketch *S, const void *A, int64_t l
   hipStream_t st = static_cast<hipStream_t>(stream);
   SAP_HIP_TRY(hipSetDevice(ctx->device));
   const int ncols = n + (b ? 1 : 0);
-  size_t got = 0;
-  s = ensure_workspace_upto(ctx, apply_workspace_bytes(ctx, S->m, S->zeta, S->d, ncols, y_type) + 256,
-                            apply_workspace_wanted(ctx, S->m, S->zeta, S->d, n, lda, b != nullptr, a_type, y_type) + 256,
-                            &got, st);
+  const size_t needed = apply_workspace_bytes(ctx, S->m, S->zeta, S->d, ncols, y_type);
+  s = ensure_workspace(ctx, needed + 256, st);
   if (s != SAP_OK) return s;
   hipEvent_t pb = prof_begin(ctx, st);
-  s = launch_apply(ctx, S, A, lda, a_type, b, n, Y, ldy, y_type, ctx->ws, got, st);
+  s = launch_apply_optional(ctx, S, A, lda, a_type, b, n, Y, ldy, y_type, ctx->ws,
+                            needed > kApplyNoScratch ? needed : 0, st);
   prof_end(ctx, kProfApply, pb, st);
   return s;
 }
@@ -488,20 +506,14 @@ static sap_status solve_dense(sap_ctx *ctx, const sap_problem *prob, const sap_p
   const size_t bytes_lsqr = lsqr_workspace_bytes(ctx, m, n);
   size_t scratch = bytes_apply > bytes_qr ? bytes_apply : bytes_qr;
   scratch = scratch > bytes_lsqr ? scratch : bytes_lsqr;
-  const size_t scratch_fast =
-      std::max(scratch, apply_workspace_wanted(ctx, m, par->zeta, d, n,
-                                               mode == SAP_MODE_MIXED_BF16SA ? (n + 7) / 8 * 8 : prob->lda, true,
-                                               mode == SAP_MODE_MIXED_BF16SA ? SAP_BF16 : prob->a_type, y_type));
   const bool bf16sa = mode == SAP_MODE_MIXED_BF16SA;
   const int64_t ld_bf = (static_cast<int64_t>(n) + 7) / 8 * 8;
   const size_t bytes_bf = bf16sa ? static_cast<size_t>(m) * ld_bf * sizeof(__hip_bfloat16) : 0;
   const size_t bytes_ss = ss ? sstep_workspace_bytes(n, ss->s) : 0;
-  const size_t fixed_bytes =
-      10 * 256 + bytes_flags + bytes_idx + bytes_sign + bytes_Y + bytes_tau + bytes_bf + bytes_ss;
-  size_t got = 0;
-  s = ensure_workspace_upto(ctx, fixed_bytes + scratch, fixed_bytes + scratch_fast, &got, st);
+  const size_t total =
+      10 * 256 + bytes_flags + bytes_idx + bytes_sign + bytes_Y + bytes_tau + bytes_bf + bytes_ss + scratch;
+  s = ensure_workspace(ctx, total, st);
   if (s != SAP_OK) return s;
-  scratch = got - fixed_bytes;
   Carve cv(ctx->ws);
   SolveFlags *flags = cv.take<SolveFlags>(1);
   int32_t *idx = cv.take<int32_t>(static_cast<size_t>(m) * par->zeta);
@@ -537,8 +549,8 @@ static sap_status solve_dense(sap_ctx *ctx, const sap_problem *prob, const sap_p
     SAP_HIP_TRY(hipGetLastError());
   }
   hipEvent_t pb_apply = prof_begin(ctx, st);
-  s = bf16sa ? launch_apply(ctx, &S, Abf, ld_bf, SAP_BF16, prob->b, n, Y, d, y_type, work, scratch, st)
-             : launch_apply(ctx, &S, prob->A, prob->lda, prob->a_type, prob->b, n, Y, d, y_type, work, scratch, st);
+  s = launch_apply_optional(ctx, &S, bf16sa ? Abf : prob->A, bf16sa ? ld_bf : prob->lda,
+                            bf16sa ? SAP_BF16 : prob->a_type, prob->b, n, Y, d, y_type, work, scratch, st);
   if (s != SAP_OK) return s;
   prof_end(ctx, kProfApply, pb_apply, st);
   SAP_HIP_TRY(hipEventRecord(ev[2], st));

@@ -847,7 +847,7 @@ sap_status apply_scratch_init(sap_ctx *ctx) {
 size_t apply_workspace_bytes(sap_ctx *ctx, int64_t m, int zeta, int d, int ncols, sap_dtype y_type) {
   const size_t es = (y_type == SAP_F64) ? 8 : 4;
   const ApplyPlan p = make_plan(ctx->num_cus, m, d, ncols, es);
-  size_t bytes = 8 * 256;
+  size_t bytes = kApplyNoScratch;
   if (p.nslices > 1) bytes += static_cast<size_t>(p.nslices) * d * ncols * es;
   if (zeta == 8 && p.nranges == 1 && d <= 65535 &&
       static_cast<double>(p.nstrips) * static_cast<double>(m) * 40.0 >= kCompactMinRereadBytes)
@@ -855,12 +855,13 @@ size_t apply_workspace_bytes(sap_ctx *ctx, int64_t m, int zeta, int d, int ncols
   return bytes;
 }
 
-// The same with what the gather form and finer slices use when they may.
+// What the gather form, finer slices and a packed copy use when they may; 0 for
+// an apply that writes Y alone.
 size_t apply_workspace_wanted(sap_ctx *ctx, int64_t m, int zeta, int d, int n, int64_t lda, bool with_b,
                               sap_dtype a_type, sap_dtype y_type) {
   const FullPlan f = full_plan(ctx->num_cus, m, zeta, d, n, lda, with_b, a_type, y_type == SAP_F64 ? 8 : 4);
-  return std::max(apply_workspace_bytes(ctx, m, zeta, d, n + (with_b ? 1 : 0), y_type),
-                  std::max(f.scatter_bytes, f.gather_bytes) + 1024);
+  if (!f.g.use && !f.pack && f.all.nslices == 1) return 0;
+  return (f.g.use ? f.gather_bytes : f.scatter_bytes) + 1024;
 }
 
 sap_status launch_apply(sap_ctx *ctx, const sps_sketch *S, const void *A, int64_t lda,

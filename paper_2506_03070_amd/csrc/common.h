@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "../../include/sap.h"
+#include "scratch.h"
 
 namespace sap {
 
@@ -193,7 +194,13 @@ struct LsqrState {
 
 namespace sap {
 struct Server;
-}
+
+struct HipMem {
+  bool alloc(void **p, size_t bytes);
+  void free(void *p);
+  size_t available();
+};
+}  // namespace sap
 
 struct sap_ctx {
   sap::Server *server = nullptr;  // served form (continuous batching), created on demand
@@ -203,6 +210,10 @@ struct sap_ctx {
 
   void *ws = nullptr;
   size_t ws_size = 0;
+  // what the sketch apply runs faster with, beside the workspace (within the
+  // same budget, which the workspace has the first claim to)
+  sap::HipMem apply_mem;
+  sap::OptionalScratch<sap::HipMem> apply_opt;
   // device address of this GPU's copy of the static scratch array used by
   // sps_apply_noalloc (set once at sap_create; never allocated or freed)
   void *apply_scratch = nullptr;
@@ -231,10 +242,6 @@ sap_status hip_fail(sap_ctx *ctx, hipError_t e, const char *what);
 // Grow the context workspace to at least `bytes` (synchronises `stream` when
 // it has to reallocate).  Returns SAP_ENOMEM beyond the budget.
 sap_status ensure_workspace(sap_ctx *ctx, size_t bytes, hipStream_t stream);
-// The same for `wanted` bytes where the budget and the device's memory allow
-// it, else for `needed`; *got receives which of the two.
-sap_status ensure_workspace_upto(sap_ctx *ctx, size_t needed, size_t wanted, size_t *got, hipStream_t stream);
-
 // Bump allocator over a workspace region (256-byte aligned pieces).
 struct Carve {
   char *base;
@@ -261,14 +268,21 @@ void prof_resolve(sap_ctx *ctx);
 // Sketch generation (sketch.hip).
 sap_status launch_generate(sap_ctx *ctx, const sps_sketch *S, int *err_word, hipStream_t st);
 
-// Sketch apply (apply.hip): the workspace it needs, and what it can use to run
-// faster; launch_apply takes whatever it is given from the first on.
+// Sketch apply (apply.hip): the workspace it needs (kApplyNoScratch: none, it
+// writes Y alone), and what it can use to run faster (0: no more than that);
+// launch_apply runs the form that work_bytes has room for.
+constexpr size_t kApplyNoScratch = 8 * 256;
 size_t apply_workspace_bytes(sap_ctx *ctx, int64_t m, int zeta, int d, int ncols, sap_dtype y_type);
 size_t apply_workspace_wanted(sap_ctx *ctx, int64_t m, int zeta, int d, int n, int64_t lda, bool with_b,
                               sap_dtype a_type, sap_dtype y_type);
 sap_status launch_apply(sap_ctx *ctx, const sps_sketch *S, const void *A, int64_t lda,
                         sap_dtype a_type, const double *b, int n, void *Y, int64_t ldy,
                         sap_dtype y_type, void *work, size_t work_bytes, hipStream_t st);
+// The same in the context's optional scratch where that is had and work is too
+// small for the fastest form.
+sap_status launch_apply_optional(sap_ctx *ctx, const sps_sketch *S, const void *A, int64_t lda, sap_dtype a_type,
+                                 const double *b, int n, void *Y, int64_t ldy, sap_dtype y_type, void *work,
+                                 size_t work_bytes, hipStream_t st);
 
 // Static scratch of the allocation-free apply (apply.hip): its size, and the
 // lookup of this device's copy (once per context, with the device current).

@@ -96,12 +96,8 @@ sap_status calibrate(sap_ctx *ctx, SelectCache &cache, const sap_problem *prob, 
   const size_t total = 8 * 256 + static_cast<size_t>(ms) * zeta * sizeof(int32_t) + ms * sizeof(uint64_t) +
                        static_cast<size_t>(dmax) * nc * sizeof(double) + 3 * static_cast<size_t>(nc) * sizeof(double) +
                        sizeof(int) * 4 + scratch;
-  size_t wanted = scratch;
-  for (int d : need_d) wanted = std::max(wanted, apply_workspace_wanted(ctx, ms, zeta, d, n, prob->lda, true, at, SAP_F64));
-  size_t got = 0;
-  sap_status s = ensure_workspace_upto(ctx, total, total - scratch + wanted, &got, st);
+  sap_status s = ensure_workspace(ctx, total, st);
   if (s != SAP_OK) return s;
-  scratch = got - (total - scratch);
   Carve cv(ctx->ws);
   int32_t *idx = cv.take<int32_t>(static_cast<size_t>(ms) * zeta);
   uint64_t *sign = cv.take<uint64_t>(ms);
@@ -130,11 +126,11 @@ sap_status calibrate(sap_ctx *ctx, SelectCache &cache, const sap_problem *prob, 
     s = launch_generate(ctx, &S, gen_err, st);
     if (s != SAP_OK) return s;
     // warm the kernels at this shape once, then time
-    s = launch_apply(ctx, &S, prob->A, prob->lda, at, prob->b, n, Y, d, SAP_F64, work, scratch, st);
+    s = launch_apply_optional(ctx, &S, prob->A, prob->lda, at, prob->b, n, Y, d, SAP_F64, work, scratch, st);
     if (s != SAP_OK) return s;
     double t_apply = 0.0, t_qr = 0.0;
     s = timed(ctx, st, e0, e1, &t_apply, [&] {
-      return launch_apply(ctx, &S, prob->A, prob->lda, at, prob->b, n, Y, d, SAP_F64, work, scratch, st);
+      return launch_apply_optional(ctx, &S, prob->A, prob->lda, at, prob->b, n, Y, d, SAP_F64, work, scratch, st);
     });
     if (s != SAP_OK) return s;
     s = timed(ctx, st, e0, e1, &t_qr, [&] { return launch_qr(ctx, Y, d, d, nc, tau, work, st); });
