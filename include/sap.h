@@ -138,9 +138,13 @@ sap_status sps_generate(sap_ctx *ctx, const sps_sketch *S, void *stream);
  * lda >= n, dtype a_type in {F64, F32, BF16}.  b: device, m doubles, or NULL
  * (then Y has n columns).  Y: device, column-major d x (n + (b != NULL)),
  * ldy >= d, dtype y_type in {F64, F32}; it is overwritten.  Accumulation is
- * in y_type; the 1/sqrt(zeta) scale is applied once after summation.
- * Asynchronous on `stream`.  Errors: SAP_EINVAL (shapes, dtypes, NULL),
- * SAP_ENOMEM (partial-sum workspace). */
+ * in FP64; the 1/sqrt(zeta) scale is applied once after summation.
+ * Asynchronous on `stream`.  Scratch that the call is only faster with is shared
+ * by the context's calls, which the library orders across streams; the partial
+ * sums of an apply that cannot do without them are in the context's workspace, as
+ * every other call's, and calls that overlap in time there must be ordered by the
+ * caller.  A captured call uses the workspace alone.  Errors: SAP_EINVAL (shapes,
+ * dtypes, NULL), SAP_ENOMEM (partial-sum workspace). */
 sap_status sps_apply(sap_ctx *ctx, const sps_sketch *S, const void *A, int64_t lda,
                      sap_dtype a_type, const double *b, int32_t n, void *Y, int64_t ldy,
                      sap_dtype y_type, void *stream);

@@ -36,7 +36,10 @@ bool HipMem::alloc(void **p, size_t bytes) {
   (void)hipGetLastError();
   return false;
 }
-void HipMem::free(void *p) { (void)hipFree(p); }
+void HipMem::free(void *p) {
+  if (used) (void)hipEventSynchronize(last_use);
+  (void)hipFree(p);
+}
 size_t HipMem::available() {
   size_t free_b = 0, total_b = 0;
   return hipMemGetInfo(&free_b, &total_b) == hipSuccess ? free_b : 0;
@@ -66,15 +69,26 @@ sap_status ensure_workspace(sap_ctx *ctx, size_t bytes, hipStream_t stream) {
   return SAP_OK;
 }
 
+static bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();  // the null stream beside another stream's capture
+  return true;
+}
+
 sap_status launch_apply_optional(sap_ctx *ctx, const sps_sketch *S, const void *A, int64_t lda, sap_dtype a_type,
                                  const double *b, int n, void *Y, int64_t ldy, sap_dtype y_type, void *work,
                                  size_t work_bytes, hipStream_t st) {
   const size_t wanted = apply_workspace_wanted(ctx, S->m, S->zeta, S->d, n, lda, b != nullptr, a_type, y_type);
-  if (wanted > work_bytes && ctx->apply_opt.reserve(ctx->apply_mem, wanted, ctx->budget - ctx->ws_size)) {
-    work = ctx->apply_opt.base;
-    work_bytes = ctx->apply_opt.size;
-  }
-  return launch_apply(ctx, S, A, lda, a_type, b, n, Y, ldy, y_type, work, work_bytes, st);
+  HipMem &mem = ctx->apply_mem;
+  if (wanted <= work_bytes || capturing(st) || !ctx->apply_opt.reserve(mem, wanted, ctx->budget - ctx->ws_size))
+    return launch_apply(ctx, S, A, lda, a_type, b, n, Y, ldy, y_type, work, work_bytes, st);
+  if (mem.used) SAP_HIP_TRY(hipStreamWaitEvent(st, mem.last_use, 0));
+  const sap_status s =
+      launch_apply(ctx, S, A, lda, a_type, b, n, Y, ldy, y_type, ctx->apply_opt.base, ctx->apply_opt.size, st);
+  mem.used = true;
+  SAP_HIP_TRY(hipEventRecord(mem.last_use, st));
+  return s;
 }
 
 static hipEvent_t take_event(sap_ctx *ctx) {
@@ -216,9 +230,11 @@ sap_status sap_create(sap_ctx **out, int device, size_t hbm_budget) {
     return SAP_EDEVICE;
   }
   if (hipHostMalloc(&ctx->pinned, kPinnedBytes, hipHostMallocDefault) != hipSuccess ||
+      hipEventCreateWithFlags(&ctx->apply_mem.last_use, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess ||
       hipEventCreateWithFlags(&ctx->batch_ev[0], hipEventDisableTiming) != hipSuccess ||
       hipEventCreateWithFlags(&ctx->batch_ev[1], hipEventDisableTiming) != hipSuccess) {
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
+    if (ctx->apply_mem.last_use) (void)hipEventDestroy(ctx->apply_mem.last_use);
     for (hipEvent_t e : ctx->batch_ev)
       if (e) (void)hipEventDestroy(e);
     delete ctx;
@@ -242,6 +258,7 @@ void sap_destroy(sap_ctx *ctx) {
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
   if (ctx->ws) (void)hipFree(ctx->ws);
   ctx->apply_opt.release(ctx->apply_mem);
+  (void)hipEventDestroy(ctx->apply_mem.last_use);
   delete ctx;
 }
 

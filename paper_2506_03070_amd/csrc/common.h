@@ -196,6 +196,10 @@ namespace sap {
 struct Server;
 
 struct HipMem {
+  // The optional scratch's last use: calls on different streams share the buffer,
+  // so each one's stream waits for the one before it.
+  hipEvent_t last_use = nullptr;
+  bool used = false;
   bool alloc(void **p, size_t bytes);
   void free(void *p);
   size_t available();
@@ -279,7 +283,8 @@ sap_status launch_apply(sap_ctx *ctx, const sps_sketch *S, const void *A, int64_
                         sap_dtype a_type, const double *b, int n, void *Y, int64_t ldy,
                         sap_dtype y_type, void *work, size_t work_bytes, hipStream_t st);
 // The same in the context's optional scratch where that is had and work is too
-// small for the fastest form.
+// small for the fastest form.  Not while the stream is being captured: a graph
+// would keep the buffer's address and not the wait for its last use.
 sap_status launch_apply_optional(sap_ctx *ctx, const sps_sketch *S, const void *A, int64_t lda, sap_dtype a_type,
                                  const double *b, int n, void *Y, int64_t ldy, sap_dtype y_type, void *work,
                                  size_t work_bytes, hipStream_t st);
