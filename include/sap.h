@@ -451,10 +451,11 @@ sap_status sap_iteration_estimate(int32_t n, int32_t d, double eps, int32_t *ite
  * eq. (4.2)'s d, clipped to [n + 1, min(m, 16384)], it returns the one that
  * minimises apply(d) + qr(d) + (t(d) + 1) (a m + f): t(d) the eq. (4.1)
  * iteration estimate for eps, apply(d) the sketch apply timed on the first
- * min(m, 65536) rows of the caller's A and scaled to m, qr(d) the QR of that
- * d x (n + 1) sketch, and a m + f the cost of one LSQR iteration fitted from
- * iterations timed on that slab and on half of it.  The timings are taken
- * once per context for each (n, dtype, zeta, candidate d) and cached; the
+ * min(m, 65536) rows of the caller's A, in the form that all m rows take, and
+ * scaled to m, qr(d) the QR of that d x (n + 1) sketch, and a m + f the cost of
+ * one LSQR iteration fitted from iterations timed on that slab and on half of
+ * it.  The timings are taken once per context for each (n, dtype, zeta,
+ * candidate d, form of the apply) and cached; the
  * first call for a width costs roughly a few QRs.  Problems with m < 4096
  * get eq. (4.2)'s d.  Blocking on `stream`; uses the context workspace.
  * Errors: SAP_EINVAL (problem, zeta, eps outside (0, 1)), SAP_ENOMEM,

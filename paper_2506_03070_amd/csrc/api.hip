@@ -78,14 +78,15 @@ static bool capturing(hipStream_t st) {
 
 sap_status launch_apply_optional(sap_ctx *ctx, const sps_sketch *S, const void *A, int64_t lda, sap_dtype a_type,
                                  const double *b, int n, void *Y, int64_t ldy, sap_dtype y_type, void *work,
-                                 size_t work_bytes, hipStream_t st) {
-  const size_t wanted = apply_workspace_wanted(ctx, S->m, S->zeta, S->d, n, lda, b != nullptr, a_type, y_type);
+                                 size_t work_bytes, hipStream_t st, ApplyForm form) {
+  const size_t wanted =
+      apply_workspace_wanted(ctx, S->m, S->zeta, S->d, n, lda, b != nullptr, a_type, y_type, form);
   HipMem &mem = ctx->apply_mem;
   if (wanted <= work_bytes || capturing(st) || !ctx->apply_opt.reserve(mem, wanted, ctx->budget - ctx->ws_size))
-    return launch_apply(ctx, S, A, lda, a_type, b, n, Y, ldy, y_type, work, work_bytes, st);
+    return launch_apply(ctx, S, A, lda, a_type, b, n, Y, ldy, y_type, work, work_bytes, st, form);
   if (mem.used) SAP_HIP_TRY(hipStreamWaitEvent(st, mem.last_use, 0));
-  const sap_status s =
-      launch_apply(ctx, S, A, lda, a_type, b, n, Y, ldy, y_type, ctx->apply_opt.base, ctx->apply_opt.size, st);
+  const sap_status s = launch_apply(ctx, S, A, lda, a_type, b, n, Y, ldy, y_type, ctx->apply_opt.base,
+                                    ctx->apply_opt.size, st, form);
   mem.used = true;
   SAP_HIP_TRY(hipEventRecord(mem.last_use, st));
   return s;

@@ -608,6 +608,7 @@ struct GatherPlan {
   int rows = 0, ntiles = 0, nstrips = 0, nslices = 1, tiles_per_slice = 0;
   unsigned int cap = 0;  // chunks
   size_t bytes = 0;
+  double us = 0.0;
 };
 
 // The gather form for A's n columns, if it is estimated to beat the scatter
@@ -656,6 +657,7 @@ GatherPlan make_gather(int num_cus, int64_t m, int zeta, int d, int n, int64_t l
   g.cap = static_cast<unsigned>(cap);
   g.bytes = 4 * 256 + static_cast<size_t>(g.ntiles) * (kGatherWaves * g.s + 1) * sizeof(uint32_t) +
             (static_cast<size_t>(g.cap) + kSpareChunks) * kWave * 8 + part_bytes(g.nslices, d, n, es_out);
+  g.us = best + lists;
   g.use = true;
   return g;
 }
@@ -667,9 +669,10 @@ struct FullPlan {
   GatherPlan g;
   bool pack;
   size_t scatter_bytes, gather_bytes;
+  double us;  // estimate of the form it picks
 };
 FullPlan full_plan(int num_cus, int64_t m, int zeta, int d, int n, int64_t lda, bool with_b, sap_dtype a_type,
-                   size_t es) {
+                   size_t es, ApplyForm form) {
   FullPlan f;
   const int ncols = n + (with_b ? 1 : 0);
   const ApplyPlan p = make_plan(num_cus, m, d, ncols, sizeof(double));
@@ -680,8 +683,10 @@ FullPlan full_plan(int num_cus, int64_t m, int zeta, int d, int n, int64_t lda, 
   f.scatter_bytes = part_bytes(f.all.nslices, d, ncols, es) + copy + 1024;
   f.a = make_plan(num_cus, m, d, n, sizeof(double));
   f.b = fine_plan(num_cus, m, zeta, d, 1, es, make_plan(num_cus, m, d, 1, sizeof(double)), false, true);
+  f.us = scatter_us(num_cus, zeta, f.all, f.pack, near) + parts_us(f.all.nslices, d, ncols, es);
   f.g = make_gather(num_cus, m, zeta, d, n, lda, a_type, es,
-                    scatter_us(num_cus, zeta, f.all, f.pack, near) + parts_us(f.all.nslices, d, ncols, es));
+                    form == kApplyScatter ? 0.0 : form == kApplyGather ? INFINITY : f.us);
+  if (f.g.use) f.us = f.g.us;
   f.gather_bytes = f.g.use ? f.g.bytes + part_bytes(f.a.nslices, d, n, es) + copy +
                                  (with_b ? part_bytes(f.b.nslices, d, 1, es) : 0) + 2048
                            : 0;
@@ -799,10 +804,11 @@ sap_status gather(sap_ctx *ctx, const sps_sketch *S, const TA *A, int64_t lda, i
 
 template <typename TA, typename TO>
 sap_status apply_typed(sap_ctx *ctx, const sps_sketch *S, const TA *A, int64_t lda, const double *b, int n,
-                       sap_dtype a_type, TO *Y, int64_t ldy, void *work, size_t work_bytes, hipStream_t st) {
+                       sap_dtype a_type, TO *Y, int64_t ldy, void *work, size_t work_bytes, hipStream_t st,
+                       ApplyForm form) {
   const int ncols = n + (b != nullptr ? 1 : 0);
   Carve cv(work);
-  FullPlan f = full_plan(ctx->num_cus, S->m, S->zeta, S->d, n, lda, b != nullptr, a_type, sizeof(TO));
+  FullPlan f = full_plan(ctx->num_cus, S->m, S->zeta, S->d, n, lda, b != nullptr, a_type, sizeof(TO), form);
   if (f.g.use && f.gather_bytes <= work_bytes) {
     // A's columns by the gather (by the scatter form if the sketch is too
     // uneven for it), b's by the scatter form: one column
@@ -858,18 +864,30 @@ size_t apply_workspace_bytes(sap_ctx *ctx, int64_t m, int zeta, int d, int ncols
 // What the gather form, finer slices and a packed copy use when they may; 0 for
 // an apply that writes Y alone.
 size_t apply_workspace_wanted(sap_ctx *ctx, int64_t m, int zeta, int d, int n, int64_t lda, bool with_b,
-                              sap_dtype a_type, sap_dtype y_type) {
-  const FullPlan f = full_plan(ctx->num_cus, m, zeta, d, n, lda, with_b, a_type, y_type == SAP_F64 ? 8 : 4);
+                              sap_dtype a_type, sap_dtype y_type, ApplyForm form) {
+  const FullPlan f = full_plan(ctx->num_cus, m, zeta, d, n, lda, with_b, a_type, y_type == SAP_F64 ? 8 : 4, form);
   if (!f.g.use && !f.pack && f.all.nslices == 1) return 0;
   return (f.g.use ? f.gather_bytes : f.scatter_bytes) + 1024;
 }
 
+ApplyForm apply_form(sap_ctx *ctx, int64_t m, int zeta, int d, int n, int64_t lda, bool with_b, sap_dtype a_type,
+                     sap_dtype y_type) {
+  return full_plan(ctx->num_cus, m, zeta, d, n, lda, with_b, a_type, y_type == SAP_F64 ? 8 : 4, kApplyChoose).g.use
+             ? kApplyGather
+             : kApplyScatter;
+}
+
+double apply_estimate_us(sap_ctx *ctx, int64_t m, int zeta, int d, int n, int64_t lda, bool with_b, sap_dtype a_type,
+                         sap_dtype y_type, ApplyForm form) {
+  return full_plan(ctx->num_cus, m, zeta, d, n, lda, with_b, a_type, y_type == SAP_F64 ? 8 : 4, form).us;
+}
+
 sap_status launch_apply(sap_ctx *ctx, const sps_sketch *S, const void *A, int64_t lda,
                         sap_dtype a_type, const double *b, int n, void *Y, int64_t ldy,
-                        sap_dtype y_type, void *work, size_t work_bytes, hipStream_t st) {
+                        sap_dtype y_type, void *work, size_t work_bytes, hipStream_t st, ApplyForm form) {
 #define SAP_APPLY(TA, TO)                                                                                      \
   return apply_typed<TA, TO>(ctx, S, static_cast<const TA *>(A), lda, b, n, a_type, static_cast<TO *>(Y), ldy, \
-                             work, work_bytes, st)
+                             work, work_bytes, st, form)
   if (y_type == SAP_F64) {
     switch (a_type) {
       case SAP_F64: SAP_APPLY(double, double);

@@ -274,20 +274,28 @@ sap_status launch_generate(sap_ctx *ctx, const sps_sketch *S, int *err_word, hip
 
 // Sketch apply (apply.hip): the workspace it needs (kApplyNoScratch: none, it
 // writes Y alone), and what it can use to run faster (0: no more than that);
-// launch_apply runs the form that work_bytes has room for.
+// launch_apply runs the form that work_bytes has room for, of the two that it
+// chooses between the one given.
+enum ApplyForm { kApplyChoose, kApplyScatter, kApplyGather };
 constexpr size_t kApplyNoScratch = 8 * 256;
 size_t apply_workspace_bytes(sap_ctx *ctx, int64_t m, int zeta, int d, int ncols, sap_dtype y_type);
 size_t apply_workspace_wanted(sap_ctx *ctx, int64_t m, int zeta, int d, int n, int64_t lda, bool with_b,
-                              sap_dtype a_type, sap_dtype y_type);
+                              sap_dtype a_type, sap_dtype y_type, ApplyForm form = kApplyChoose);
 sap_status launch_apply(sap_ctx *ctx, const sps_sketch *S, const void *A, int64_t lda,
                         sap_dtype a_type, const double *b, int n, void *Y, int64_t ldy,
-                        sap_dtype y_type, void *work, size_t work_bytes, hipStream_t st);
+                        sap_dtype y_type, void *work, size_t work_bytes, hipStream_t st,
+                        ApplyForm form = kApplyChoose);
 // The same in the context's optional scratch where that is had and work is too
 // small for the fastest form.  Not while the stream is being captured: a graph
 // would keep the buffer's address and not the wait for its last use.
 sap_status launch_apply_optional(sap_ctx *ctx, const sps_sketch *S, const void *A, int64_t lda, sap_dtype a_type,
                                  const double *b, int n, void *Y, int64_t ldy, sap_dtype y_type, void *work,
-                                 size_t work_bytes, hipStream_t st);
+                                 size_t work_bytes, hipStream_t st, ApplyForm form = kApplyChoose);
+// The form that it chooses, and the time estimate by which.
+ApplyForm apply_form(sap_ctx *ctx, int64_t m, int zeta, int d, int n, int64_t lda, bool with_b, sap_dtype a_type,
+                     sap_dtype y_type);
+double apply_estimate_us(sap_ctx *ctx, int64_t m, int zeta, int d, int n, int64_t lda, bool with_b, sap_dtype a_type,
+                         sap_dtype y_type, ApplyForm form);
 
 // Static scratch of the allocation-free apply (apply.hip): its size, and the
 // lookup of this device's copy (once per context, with the device current).

@@ -3,11 +3,15 @@
 // Eq. (4.2) balances the QR work d n^2 against the iteration work t(d) m n
 // with the two unit costs taken equal, and assumes the sketch costs the same
 // at every d.  On this GPU neither holds exactly: the apply's cost steps with
-// the LDS strip width that d allows, and the QR's with its panel path.  So
-// the candidates are priced with the library's own kernels, timed on a slab
-// of the caller's problem, once per context and (n, dtype, zeta, d):
-//   apply(d): the sketch apply of the first m_s = min(m, 65536) rows at d,
-//             scaled by m / m_s;
+// its form and strip width, which d, m and A's size in memory decide, and the
+// QR's with its panel path.  So the candidates are priced with the library's
+// own kernels, timed on a slab of the caller's problem, once per context and
+// (n, dtype, zeta, d, form of the apply):
+//   apply(d): the sketch apply of the first m_s = min(m, 65536) rows at d, in
+//             the form that the whole problem takes, times the ratio of the
+//             apply's own estimates for m rows and for the slab (at 2^20 x 500
+//             FP64, d = 5000, the slab by itself would take the scatter, which
+//             m / m_s makes 2.77 ms; the whole takes the gather, 2.03 ms);
 //   qr(d):    the Householder QR of that d x (n+1) sketch (independent of m);
 //   a m + f:  one LSQR iteration, from iterations timed on the slab and on
 //             half of it (each as the difference of a 9- and a 3-iteration
@@ -26,11 +30,12 @@ namespace sap {
 
 struct SelectCache {
   struct Entry {
-    double apply_ms_per_row = 0.0;  // apply time per row of A at this d
+    double apply_ms = 0.0;  // apply time of the slab at this d
+    double apply_us = 0.0;  // the apply's own estimate of it
     double qr_ms = 0.0;
   };
-  // (n, dtype, zeta, d) -> timings; (n, dtype) -> iteration fit (a per row, f)
-  std::map<std::tuple<int, int, int, int>, Entry> phase;
+  // (n, dtype, zeta, d, form) -> timings; (n, dtype) -> iteration fit (a per row, f)
+  std::map<std::tuple<int, int, int, int, int>, Entry> phase;
   std::map<std::tuple<int, int>, std::pair<double, double>> iter_fit;
 };
 
@@ -61,6 +66,14 @@ std::vector<int> candidates(int64_t m, int n, double eps) {
   std::sort(c.begin(), c.end());
   c.erase(std::unique(c.begin(), c.end()), c.end());
   return c;
+}
+
+// The apply's form for the whole problem at d, and the key of d's timings.
+ApplyForm form_of(sap_ctx *ctx, const sap_problem *p, int zeta, int d) {
+  return apply_form(ctx, p->m, zeta, d, p->n, p->lda, true, p->a_type, SAP_F64);
+}
+std::tuple<int, int, int, int, int> phase_key(sap_ctx *ctx, const sap_problem *p, int zeta, int d) {
+  return std::make_tuple(p->n, static_cast<int>(p->a_type), zeta, d, static_cast<int>(form_of(ctx, p, zeta, d)));
 }
 
 // Time (ms) of a blocking host call bracketed by events on `st`.
@@ -126,17 +139,19 @@ sap_status calibrate(sap_ctx *ctx, SelectCache &cache, const sap_problem *prob, 
     s = launch_generate(ctx, &S, gen_err, st);
     if (s != SAP_OK) return s;
     // warm the kernels at this shape once, then time
-    s = launch_apply_optional(ctx, &S, prob->A, prob->lda, at, prob->b, n, Y, d, SAP_F64, work, scratch, st);
+    const ApplyForm form = form_of(ctx, prob, zeta, d);
+    s = launch_apply_optional(ctx, &S, prob->A, prob->lda, at, prob->b, n, Y, d, SAP_F64, work, scratch, st, form);
     if (s != SAP_OK) return s;
     double t_apply = 0.0, t_qr = 0.0;
     s = timed(ctx, st, e0, e1, &t_apply, [&] {
-      return launch_apply_optional(ctx, &S, prob->A, prob->lda, at, prob->b, n, Y, d, SAP_F64, work, scratch, st);
+      return launch_apply_optional(ctx, &S, prob->A, prob->lda, at, prob->b, n, Y, d, SAP_F64, work, scratch, st, form);
     });
     if (s != SAP_OK) return s;
     s = timed(ctx, st, e0, e1, &t_qr, [&] { return launch_qr(ctx, Y, d, d, nc, tau, work, st); });
     if (s != SAP_OK) return s;
-    SelectCache::Entry &en = cache.phase[std::make_tuple(n, static_cast<int>(at), zeta, d)];
-    en.apply_ms_per_row = t_apply / static_cast<double>(ms);
+    SelectCache::Entry &en = cache.phase[phase_key(ctx, prob, zeta, d)];
+    en.apply_ms = t_apply;
+    en.apply_us = apply_estimate_us(ctx, ms, zeta, d, n, prob->lda, true, at, SAP_F64, form);
     en.qr_ms = t_qr;
   }
   if (need_fit) {
@@ -173,6 +188,12 @@ sap_status calibrate(sap_ctx *ctx, SelectCache &cache, const sap_problem *prob, 
   return SAP_OK;
 }
 
+// apply(d) of the whole problem, in ms.
+double price_apply(sap_ctx *ctx, const SelectCache::Entry &en, const sap_problem *prob, int zeta, int d) {
+  return en.apply_ms / en.apply_us * apply_estimate_us(ctx, prob->m, zeta, d, prob->n, prob->lda, true, prob->a_type,
+                                                       SAP_F64, form_of(ctx, prob, zeta, d));
+}
+
 }  // namespace
 
 sap_status choose_d(sap_ctx *ctx, const sap_problem *prob, int zeta, double eps, int32_t *d, hipStream_t st) {
@@ -189,7 +210,7 @@ sap_status choose_d(sap_ctx *ctx, const sap_problem *prob, int zeta, double eps,
   const std::vector<int> cand = candidates(m, n, eps);
   std::vector<int> need;
   for (int dc : cand)
-    if (!cache.phase.count(std::make_tuple(n, static_cast<int>(prob->a_type), zeta, dc))) need.push_back(dc);
+    if (!cache.phase.count(phase_key(ctx, prob, zeta, dc))) need.push_back(dc);
   const bool need_fit = !cache.iter_fit.count(std::make_tuple(n, static_cast<int>(prob->a_type)));
   if (!need.empty() || need_fit) {
     std::vector<int> nd = need.empty() ? std::vector<int>{cand.back()} : need;
@@ -201,10 +222,10 @@ sap_status choose_d(sap_ctx *ctx, const sap_problem *prob, int zeta, double eps,
   double best = INFINITY;
   int best_d = cand.front();
   for (int dc : cand) {
-    const SelectCache::Entry &en = cache.phase[std::make_tuple(n, static_cast<int>(prob->a_type), zeta, dc)];
+    const SelectCache::Entry &en = cache.phase[phase_key(ctx, prob, zeta, dc)];
     int32_t t = 0;
     if (sap_iteration_estimate(n, dc, eps, &t) != SAP_OK) continue;
-    const double cost = en.apply_ms_per_row * static_cast<double>(m) + en.qr_ms + (t + 1.0) * per_iter;
+    const double cost = price_apply(ctx, en, prob, zeta, dc) + en.qr_ms + (t + 1.0) * per_iter;
     if (cost < best) {
       best = cost;
       best_d = dc;
@@ -230,4 +251,15 @@ extern "C" sap_status sap_choose_d(sap_ctx *ctx, const sap_problem *prob, int32_
   if (!(eps > 0.0 && eps < 1.0)) return fail(ctx, SAP_EINVAL, "sap_choose_d: eps must be in (0, 1)");
   SAP_HIP_TRY(hipSetDevice(ctx->device));
   return choose_d(ctx, prob, zeta, eps, d, static_cast<hipStream_t>(stream));
+}
+
+// For the tests: apply(d) as sap_choose_d priced it (after it, for one of its candidates).
+extern "C" sap_status sap_internal_price_apply(sap_ctx *ctx, const sap_problem *prob, int32_t zeta, int32_t d,
+                                               double *ms) {
+  if (!ctx || !ctx->select_cache || !prob || !ms) return SAP_EINVAL;
+  const auto &phase = static_cast<SelectCache *>(ctx->select_cache)->phase;
+  const auto it = phase.find(phase_key(ctx, prob, zeta, d));
+  if (it == phase.end()) return SAP_EINVAL;
+  *ms = price_apply(ctx, it->second, prob, zeta, d);
+  return SAP_OK;
 }
