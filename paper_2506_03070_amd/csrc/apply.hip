@@ -906,3 +906,13 @@ sap_status launch_apply(sap_ctx *ctx, const sps_sketch *S, const void *A, int64_
 }
 
 }  // namespace sap
+
+// For the tests: 2 if this apply runs the gather form where it has the scratch
+// that it asks for, else 1.
+extern "C" int sap_internal_apply_form(sap_ctx *ctx, int64_t m, int zeta, int d, int n, int64_t lda, int with_b,
+                                       int a_type, int y_type) {
+  return sap::apply_form(ctx, m, zeta, d, n, lda, with_b != 0, static_cast<sap_dtype>(a_type),
+                         static_cast<sap_dtype>(y_type)) == sap::kApplyGather
+             ? 2
+             : 1;
+}
