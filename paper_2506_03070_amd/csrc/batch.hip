@@ -1566,6 +1566,7 @@ int64_t serve_rows_per_chunk(int n, sap_dtype at) {
 }
 constexpr int kServeMaxChunks = 1 << 20;
 constexpr int kServeMaxApply = 1 << 20;
+static_assert(kServeMaxApply >= (1024 / 4 + 1) * kMaxApplySlices, "one request fits");
 
 // A device error ends serving: every request not finished yet fails.
 void serve_fail_all(Server *S, const std::string &msg, std::vector<ServeRequest *> &fresh) {
@@ -1786,10 +1787,15 @@ void serve_loop(Server *S) {
           ++it;
         }
       }
-      // admit in arrival order while the head of the queue fits
+      // admit in arrival order while the head of the queue fits, in the arena and
+      // in the round's table of apply work items (one request always does)
+      int64_t napply = 0;
       const auto now = std::chrono::steady_clock::now();
       while (!S->queued.empty() && static_cast<int>(S->active.size() + fresh.size()) < S->max_slots) {
         ServeRequest *r = S->queued.front();
+        napply += static_cast<int64_t>(batch_apply_strips(r->par.d, r->prob.n)) *
+                  apply_slices(r->prob.m, r->prob.n, r->par.d);
+        if (napply > kServeMaxApply) break;
         size_t off = 0;
         if (!S->arena.alloc(r->bytes, &off)) break;
         r->offset = off;
