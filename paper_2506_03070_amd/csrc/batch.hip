@@ -112,8 +112,9 @@ constexpr int kXcdsB = 8;
 // in the packed form (16 bytes a row in it.idx, no it.sign; d <= 4096 here).
 __host__ __device__ inline bool packed_sketch(int zeta) { return zeta == 8; }
 
-template <int ZMAX>
-__global__ __launch_bounds__(256) void batch_generate_kernel(const BatchItem *__restrict__ items, int count,
+// (one launch for the problems of that form, one for the others where there are any)
+template <int ZMAX, bool PACKED>
+__global__ __launch_bounds__(256, ZMAX == 8 ? 3 : 1) void batch_generate_kernel(const BatchItem *__restrict__ items, int count,
                                                              int64_t total, int *__restrict__ err) {
   const int64_t g = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (g >= total) return;
@@ -124,8 +125,10 @@ __global__ __launch_bounds__(256) void batch_generate_kernel(const BatchItem *__
     else hi = mid - 1;
   }
   const BatchItem &it = items[lo];
-  sketch_dev::generate_column<ZMAX>(g - it.col_base, it.d, it.zeta, it.seed, it.stream, it.idx, it.sign, err,
-                                    packed_sketch(it.zeta) ? reinterpret_cast<uint4 *>(it.idx) : nullptr);
+  if (packed_sketch(it.zeta) != PACKED) return;
+  sketch_dev::generate_column<ZMAX, PACKED ? sketch_dev::kStorePacked : sketch_dev::kStoreEach>(
+      g - it.col_base, it.d, PACKED ? 8 : it.zeta, it.seed, it.stream, it.idx, it.sign, err,
+      PACKED ? reinterpret_cast<uint4 *>(it.idx) : nullptr);
 }
 
 // ---- apply -----------------------------------------------------------------
@@ -1016,19 +1019,24 @@ void carve_item(BatchItem &it, void *base, sap_dtype at, int64_t rows_per_chunk)
 sap_status setup_items(sap_ctx *ctx, BatchItem *ditems, const std::vector<BatchItem> &items, const int2 *dapply,
                        int napply, int *dflags, sap_dtype at, hipStream_t st) {
   const int count = static_cast<int>(items.size());
-  int n_max = 0, d_max = 0, zeta_max = 0;
+  int n_max = 0, d_max = 0, zeta_max = 0;  // zeta_max: of the sketches that are not packed
+  bool any_packed = false;
   int64_t total_cols = 0;
   for (const auto &it : items) {
     n_max = std::max(n_max, it.n);
     d_max = std::max(d_max, it.d);
-    zeta_max = std::max(zeta_max, it.zeta);
+    if (packed_sketch(it.zeta)) any_packed = true;
+    else zeta_max = std::max(zeta_max, it.zeta);
     total_cols = std::max(total_cols, it.col_base + it.m);
   }
   const unsigned grid = static_cast<unsigned>((total_cols + 255) / 256);
-  if (zeta_max <= 8) batch_generate_kernel<8><<<grid, 256, 0, st>>>(ditems, count, total_cols, dflags + 2);
-  else if (zeta_max <= 16) batch_generate_kernel<16><<<grid, 256, 0, st>>>(ditems, count, total_cols, dflags + 2);
-  else if (zeta_max <= 32) batch_generate_kernel<32><<<grid, 256, 0, st>>>(ditems, count, total_cols, dflags + 2);
-  else batch_generate_kernel<64><<<grid, 256, 0, st>>>(ditems, count, total_cols, dflags + 2);
+#define SAP_GENERATE(Z, P) batch_generate_kernel<Z, P><<<grid, 256, 0, st>>>(ditems, count, total_cols, dflags + 2)
+  if (any_packed) SAP_GENERATE(8, true);
+  if (zeta_max > 32) SAP_GENERATE(64, false);
+  else if (zeta_max > 16) SAP_GENERATE(32, false);
+  else if (zeta_max > 8) SAP_GENERATE(16, false);
+  else if (zeta_max > 0) SAP_GENERATE(8, false);
+#undef SAP_GENERATE
   const int per_xcd = (napply + kXcdsB - 1) / kXcdsB;
   size_t lds = 0;  // strips with a spare row
   for (const auto &it : items)

@@ -23,7 +23,7 @@ __global__ __launch_bounds__(256) void generate_kernel(int64_t m, int d, int zet
                                                        int *__restrict__ err) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= m) return;
-  generate_column<ZMAX>(i, d, zeta, seed, stream, idx, sign, err);
+  generate_column<ZMAX, sketch_dev::kStoreVector>(i, d, zeta, seed, stream, idx, sign, err);
 }
 
 }  // namespace

@@ -102,9 +102,15 @@ __device__ __forceinline__ void bitonic_sort(uint32_t (&c)[N]) {
 }
 
 // Column i of the sketch: zeta ascending distinct rows into idx[i*zeta ..]
-// and the sign word into sign[i], or (packed non-null, zeta = 8) both into
-// packed[i] (apply_dev.h).
-template <int ZMAX>
+// and the sign word into sign[i], or, kStorePacked (zeta = 8), both into
+// packed[i] (apply_dev.h).  A template argument: as branches the forms cost the
+// batched generator 11 registers and with them its third wave a SIMD.
+enum StoreForm {
+  kStoreEach,    // one store an index
+  kStoreVector,  // zeta = 8 and aligned: a lane's 32 bytes in two stores
+  kStorePacked,
+};
+template <int ZMAX, StoreForm FORM>
 __device__ __forceinline__ void generate_column(int64_t i, int d, int zeta, uint64_t seed, uint64_t stream,
                                                 int32_t *__restrict__ idx, uint64_t *__restrict__ sign,
                                                 int *__restrict__ err, uint4 *__restrict__ packed = nullptr) {
@@ -167,19 +173,18 @@ __device__ __forceinline__ void generate_column(int64_t i, int d, int zeta, uint
   }
 
   const Block4 s = philox(col, ~0ull, 0, 0, seed, stream);
-  if constexpr (ZMAX >= 8) {
-    if (packed) {
-      const uint32_t w = static_cast<uint32_t>(s.w[0]);
-      uint32_t e[8];
+  if constexpr (FORM == kStorePacked) {
+    static_assert(ZMAX == 8, "eight entries");
+    const uint32_t w = static_cast<uint32_t>(s.w[0]);
+    uint32_t e[8];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) e[k] = apply_dev::pack_entry(static_cast<int32_t>(c[k]), d, (w >> k) & 1u);
-      packed[i] = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
-      return;
-    }
+    for (int k = 0; k < 8; ++k) e[k] = apply_dev::pack_entry(static_cast<int32_t>(c[k]), d, (w >> k) & 1u);
+    packed[i] = make_uint4(e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16));
+    return;
   }
   int32_t *out = idx + i * zeta;
   bool stored = false;
-  if constexpr (ZMAX == 8) {  // a lane's 32 bytes in two stores instead of eight
+  if constexpr (ZMAX == 8 && FORM == kStoreVector) {
     if (zeta == 8 && (reinterpret_cast<uintptr_t>(idx) & 15) == 0) {
       int4 *o4 = reinterpret_cast<int4 *>(out);
       o4[0] = make_int4(c[0], c[1], c[2], c[3]);
