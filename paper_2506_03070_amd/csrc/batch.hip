@@ -288,11 +288,12 @@ __global__ __launch_bounds__(kPanelThreads) void batch_qr_first_kernel(const Bat
   for (int s = 0; s < S; ++s)
 #pragma unroll
     for (int i = 0; i < NB; ++i) V[s][i] = 0.0;
-  gram_prepare<S, NB, kPanelThreads>(P, sh, 0);
+  const bool gram = rows >= kGramRows;
+  if (gram) gram_prepare<S, NB, kPanelThreads>(P, sh, 0);
   __syncthreads();
-  if (threadIdx.x < kWave) gram_total<NB, kPanelThreads>(sh);
+  if (gram && threadIdx.x < kWave) gram_total<NB, kPanelThreads>(sh);
   factor_update<S, NB, kPanelThreads>(
-      P, V, 0.0, sh, nb, rows, 0, 0, it.tau, true, true, [](int, int, double) {}, [&](int e, double v) { it.T0[e] = v; });
+      P, V, 0.0, sh, nb, rows, 0, 0, it.tau, gram, true, [](int, int, double) {}, [&](int e, double v) { it.T0[e] = v; });
   store_columns<S, NB, kPanelThreads, 0>(it.Y, rows, rows, nb, 0, P);
 }
 
@@ -316,13 +317,14 @@ __global__ __launch_bounds__(kPanelThreads) void batch_qr_step_kernel(const Batc
   double C[S][NB], V[S][NB];
   load_columns<S, NB, kPanelThreads, 0>(base, rows, dr, ncb, 0, C);
   load_columns<S, NB, kPanelThreads, 0>(it.Y + k0 + static_cast<int64_t>(k0) * rows, rows, dr, NB, 0, V);
-  if (blockIdx.x == 0) gram_prepare<S, NB, kPanelThreads>(C, sh, NB);
+  const bool gram = dr - NB >= kGramRows;
+  if (gram && blockIdx.x == 0) gram_prepare<S, NB, kPanelThreads>(C, sh, NB);
   unit_lower<S, NB, kPanelThreads>(V, 0);
   if (blockIdx.x == 0) {
     __syncthreads();
-    if (threadIdx.x < kWave) gram_total<NB, kPanelThreads>(sh);
+    if (gram && threadIdx.x < kWave) gram_total<NB, kPanelThreads>(sh);
     factor_update<S, NB, kPanelThreads>(
-        C, V, tel, sh, ncb, dr, NB, c0, it.tau, true, true,
+        C, V, tel, sh, ncb, dr, NB, c0, it.tau, gram, true,
         [&](int r, int x, double v) {
           if (x < ncb) base[r + static_cast<int64_t>(x) * rows] = v;
         },

@@ -24,10 +24,10 @@
 // rest the rows' way out of one CU and into the next (128 KB; 4.5 us when the
 // next block waited for the flag, see kDirect below).  16.0 us with one
 // workgroup reduction per column and selects on every row: apply 6.7, factor
-// 6.5.  4000 x 1001: 3.96 -> 2.10 ms, 2000 x 501: 1.50 -> 0.79, 1026 x 257: 0.75 ->
-// 0.40, 400 x 101: 0.245 -> 0.128, 8000 x 1001: 6.67 -> 5.10, 64 x 33 (mostly column
-// by column): 0.090 -> 0.087.  2 to 5% of that goes into the Gram form's exactness
-// (factor_update in qr_dev.h): 2.05, 0.75, 0.38, 0.122, 4.92, 0.052 without.
+// 6.5.  4000 x 1001: 3.96 -> 2.10 ms, 2000 x 501: 1.50 -> 0.78, 1026 x 257: 0.75 ->
+// 0.40, 400 x 101: 0.245 -> 0.130, 8000 x 1001: 6.67 -> 4.98, 64 x 33 (mostly column
+// by column): 0.092 -> 0.072.  1 to 6% of that goes into the Gram form's exactness
+// (factor_update in qr_dev.h): 2.05, 0.75, 0.38, 0.123, 4.92 without.
 // Sketches taller than 4096 rows and wider than 192 columns take the
 // two-level form below: 64-column panels factored by the chained form, the
 // trailing matrix updated on the FP64 matrix cores.
@@ -153,15 +153,22 @@ __global__ __launch_bounds__(TH) void qr_chain_kernel(double *__restrict__ Y, in
   if (t == 0)
     for (int k = direct; k < j; ++k) wait_flag_at(k, 1);
   const auto store_t = [&](int e, double v) { store_coherent(Tall + j * NB * NB + e, v); };
-  if (j <= kWarm) gram_prepare<S, NB, TH>(C, sh, min(j, 1) * NB);
+  const bool gram = d - c0 >= kGramRows;
+  if (gram && j <= kWarm) gram_prepare<S, NB, TH>(C, sh, min(j, 1) * NB);
   bool expired = false;
-  // the first block (j = 0) makes one round without reflectors, k = -1
-  for (int k = min(j, 1) - 1; k < j; ++k) {
+  int first = min(j, 1) - 1;  // the first block makes one round without reflectors, k = -1
+  if constexpr (S == 1) {
+    if (j == 0 && !gram) {
+      factor_first_short<S, NB, TH>(C, sh, ncb, d, tau, store_t);
+      first = 0;
+    }
+  }
+  for (int k = first; k < j; ++k) {
     if (t == 0 && k >= 0 && k < direct) wait_flag_at(k, 2);
     __syncthreads();
     expired = __builtin_amdgcn_readfirstlane(failed) != 0;
     if (expired) break;
-    const bool last = k == j - 1, warm = k >= j - kWarm;
+    const bool last = k == j - 1, warm = gram && k >= j - kWarm;
     if (warm && t < kWave) gram_total<NB, TH>(sh);
     // Panel k's reflectors (a full panel: k < j) at the rows this block's
     // threads hold, and T (element e in lane e of every wave), through the

@@ -429,6 +429,10 @@ __device__ __forceinline__ double reciprocal(double a) {
 // absolute terms (the root's estimate is for normal numbers; an exactly zero
 // column is taken).  A norm whose square overflows is refused too.
 constexpr double kGramKeep = 0.9;
+// With fewer rows the rows that the update turns into R's take more than that:
+// such panels are factored column by column without asking (10 x 2: 25 -> 21 us,
+// 64 x 33: 87 -> 72).
+constexpr int kGramRows = 64;
 constexpr double kGramTiny = 1e-280;
 constexpr double kGramHuge = 1e307;
 
@@ -676,6 +680,20 @@ __device__ __forceinline__ void factor_small(PanelShared<NB, TH> &sh, int nb, do
   }
 }
 
+// T to store_t and tau, by the first wave, which wrote sh.T and sh.tauv (LDS
+// operations of a wave are in order).
+template <int NB, int TH, typename StoreT>
+__device__ __forceinline__ void publish_small(PanelShared<NB, TH> &sh, int nb, int k0, double *__restrict__ tau,
+                                              StoreT &&store_t) {
+  if (__builtin_amdgcn_readfirstlane(threadIdx.x / kWave) != 0) return;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+  int e = threadIdx.x;
+  asm volatile("" : "+v"(e));  // (as factor_small's lane)
+  if (e < NB * NB) store_t(e, sh.T[e]);
+  if (e < nb) tau[k0 + e] = sh.tauv[e];
+}
+
 // The last update of a block, C <- (I - V T^T V^T) C, and the factorisation
 // of the panel it becomes (columns k0 .. k0+nb-1, first row roff of the
 // block's rows, the matrix ending at row hi); V and tel as for wy_product (V =
@@ -710,9 +728,10 @@ __device__ __forceinline__ void factor_small(PanelShared<NB, TH> &sh, int nb, do
 // share of a quarter 1.31, 1.12, 1.36, and on correlated columns (singular values
 // 1 to 1e-6) 1.1, 1.6, 1.4 against 1.00.
 //
-// warm = false is the update alone; warm without last runs the factorisation's
-// code too, with U the identity (left out for a panel that would be refused) and
-// nothing stored.
+// warm: the panel has kGramRows rows, and gram_prepare and gram_total ran (without:
+// the update alone, or with last the column-by-column form).  warm without last
+// runs the factorisation's code too, with U the identity (left out for a panel
+// that would be refused) and nothing stored.
 template <int S, int NB, int TH, typename PutR, typename StoreT>
 __device__ __forceinline__ void factor_update(double (&C)[S][NB], const double (&V)[S][NB], double tel,
                                               PanelShared<NB, TH> &sh, int nb, int hi, int roff, int k0,
@@ -740,9 +759,9 @@ __device__ __forceinline__ void factor_update(double (&C)[S][NB], const double (
   __builtin_amdgcn_sched_barrier(0);
   double W2[NB][NB];
   spread_w2<NB>(w2, W2);
-  // refused (a round that is not the last then leaves the panel as it is: the
+  // refused: a round that is not the last then leaves the panel as it is (the
   // identity would carry a non-finite column into the ones to its right)
-  const bool slow = warm && (hi - roff < 4 * NB || __builtin_amdgcn_readfirstlane(sh.slow) != 0);
+  const bool gram = warm && __builtin_amdgcn_readfirstlane(sh.slow) == 0;
 #pragma unroll
   for (int s = 0; s < S; ++s) update_row<NB>(C[s], V[s], W2);
   if (roff >= NB)
@@ -753,7 +772,7 @@ __device__ __forceinline__ void factor_update(double (&C)[S][NB], const double (
         C[s][x] = 0.0;
       }
     });
-  if (warm && !slow) {
+  if (gram) {
     double U[NB][NB];
 #pragma unroll
     for (int y = 0; y < NB; ++y)
@@ -769,7 +788,7 @@ __device__ __forceinline__ void factor_update(double (&C)[S][NB], const double (
         C[s][x] = q;
       }
   }
-  if (last && slow) {
+  if (last && !gram) {
     __syncthreads();  // earlier users of the shared buffers are done
     factor_panel_columns<S, NB, TH>(C, sh, nb, hi - roff, roff, k0, tau);
   } else if (last) {
@@ -778,15 +797,15 @@ __device__ __forceinline__ void factor_update(double (&C)[S][NB], const double (
       for (int x = 0; x < NB; ++x) C[s][x] = sh.top[lr][x];
     });
   }
-  // the first wave wrote sh.T and sh.tauv (LDS operations of a wave are in order)
-  if (last && wave == 0) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    int e = t;
-    asm volatile("" : "+v"(e));  // (as factor_small's lane)
-    if (e < NB * NB) store_t(e, sh.T[e]);
-    if (e < nb) tau[k0 + e] = sh.tauv[e];
-  }
+  if (last) publish_small<NB, TH>(sh, nb, k0, tau, store_t);
+}
+
+// A first panel of fewer than kGramRows rows: nothing to apply and no Gram form.
+template <int S, int NB, int TH, typename StoreT>
+__device__ __forceinline__ void factor_first_short(double (&C)[S][NB], PanelShared<NB, TH> &sh, int nb, int rows,
+                                                   double *__restrict__ tau, StoreT &&store_t) {
+  factor_panel_columns<S, NB, TH>(C, sh, nb, rows, 0, 0, tau);
+  publish_small<NB, TH>(sh, nb, 0, tau, store_t);
 }
 
 }  // namespace qr_dev
