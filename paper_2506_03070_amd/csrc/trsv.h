@@ -132,16 +132,27 @@ __device__ __forceinline__ void chain_block(const double *__restrict__ M, int64_
 // a column, in registers), then the blocks above them one diagonal after the other,
 // again one a wave: the rows below summed by all lanes, the 16 x 16 triangle solved
 // by a lane a column.  (Blocks joined by products with inverses, X12 = -X11 (R12
-// X22), are not back substitution: sap_trsv at n = 64 then was 1.4 to 1.6 times as
-// far off on the R of sketches with singular values 1 to 1e-10.)
+// X22), are not back substitution: on the R of sketches with singular values 1 to
+// 1e-10 sap_trsv at n = 64 then was 1.3 times as far off as with columns taken one
+// product after the other, 1.1 times with R^T; this form 0.9.)
 // One thread a column over the whole block is a chain of 2016 dependent LDS
-// products (49 us; this form 21, joined blocks 15).
+// products (47 us at n = 1000; this form 21, joined blocks 15; n = 20: 11, 10, 12).
 constexpr int kTrsvQ = kTrsvB / 4;
 struct TrsvPrepShared {
   double Rb[kTrsvB][kTrsvB + 1];
   double X[kTrsvB][kTrsvB + 1];  // X[row][col] = (R_bb^-1)(row, col)
   double T[3 * kTrsvQ][kTrsvQ + 1];
+  double inv[kTrsvB];  // 1 / diagonal
 };
+
+// s / r from the rounded 1 / r, with the rounding of a division (the product's
+// error comes out of an fma exactly); a zero r gives what the division gives.
+// A chain of 16 divisions would be half of the kernel.
+__device__ __forceinline__ double trsv_quotient(double s, double r, double inv) {
+  const double q = s * inv;
+  const double e = fma(-q, r, s);
+  return isfinite(q) ? fma(e, inv, q) : q;
+}
 
 __device__ __forceinline__ void trsv_invert_diag_block(const double *__restrict__ R, int64_t ldr, int n, int b,
                                                        double *__restrict__ Dup, double *__restrict__ Dlo,
@@ -154,6 +165,7 @@ __device__ __forceinline__ void trsv_invert_diag_block(const double *__restrict_
     const int rr = e % kTrsvB, cc = e / kTrsvB;
     sh.Rb[rr][cc] = (rr < kn && cc < kn && rr <= cc) ? R[(k0 + rr) + static_cast<int64_t>(k0 + cc) * ldr] : 0.0;
     sh.X[rr][cc] = 0.0;
+    if (rr == cc) sh.inv[rr] = 1.0 / sh.Rb[rr][cc];
   }
   __syncthreads();
   const int i = t / kWave, c = t % kWave, o = Q * i;
@@ -164,7 +176,8 @@ __device__ __forceinline__ void trsv_invert_diag_block(const double *__restrict_
       double s = rr == c ? 1.0 : 0.0;
 #pragma unroll
       for (int k = rr + 1; k < Q; ++k) s -= sh.Rb[o + rr][o + k] * x[k];
-      x[rr] = rr <= c ? s / sh.Rb[o + rr][o + rr] : 0.0;  // rows below the diagonal stay zero
+      // rows below the diagonal stay zero
+      x[rr] = rr <= c ? trsv_quotient(s, sh.Rb[o + rr][o + rr], sh.inv[o + rr]) : 0.0;
       sh.X[o + rr][o + c] = x[rr];
     }
   }
@@ -172,14 +185,20 @@ __device__ __forceinline__ void trsv_invert_diag_block(const double *__restrict_
 #pragma unroll
   for (int dg = 1; dg < 4; ++dg) {
     const int oc = o + Q * dg;  // block (rows o .., columns oc ..)
-    if (i + dg < 4) {           // uniform
-      for (int e = c; e < Q * Q; e += kWave) {
-        const int rr = e / Q, cc = e % Q;
-        double s = 0.0;
+    if (i + dg < 4 && oc < kn) {  // uniform
+      constexpr int P = Q * Q / kWave;  // a lane's rows r0, r0 + Q / P, ... of column cc
+      const int r0 = c / Q, cc = c % Q;
+      double s[P];
+#pragma unroll
+      for (int q = 0; q < P; ++q) s[q] = 0.0;
 #pragma unroll 8
-        for (int k = Q; k < Q * (dg + 1); ++k) s += sh.Rb[o + rr][o + k] * sh.X[o + k][oc + cc];
-        sh.T[o + rr][cc] = s;
+      for (int k = Q; k < Q * (dg + 1); ++k) {
+        const double x = sh.X[o + k][oc + cc];
+#pragma unroll
+        for (int q = 0; q < P; ++q) s[q] += sh.Rb[o + r0 + q * (Q / P)][o + k] * x;
       }
+#pragma unroll
+      for (int q = 0; q < P; ++q) sh.T[o + r0 + q * (Q / P)][cc] = s[q];
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
       __builtin_amdgcn_wave_barrier();
       if (c < Q && oc + c < kn) {
@@ -189,7 +208,7 @@ __device__ __forceinline__ void trsv_invert_diag_block(const double *__restrict_
           double s = -sh.T[o + rr][c];
 #pragma unroll
           for (int k = rr + 1; k < Q; ++k) s -= sh.Rb[o + rr][o + k] * x[k];
-          x[rr] = s / sh.Rb[o + rr][o + rr];
+          x[rr] = trsv_quotient(s, sh.Rb[o + rr][o + rr], sh.inv[o + rr]);
           sh.X[o + rr][oc + c] = x[rr];
         }
       }
