@@ -31,13 +31,41 @@ sap_status hip_fail(sap_ctx *ctx, hipError_t e, const char *what) {
   return fail(ctx, SAP_EDEVICE, msg);
 }
 
+static bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();  // the null stream beside another stream's capture
+  return true;
+}
+
+// Orders `st` after the last use; false where that cannot be had.
+bool HipMem::enter(hipStream_t st) {
+  if (!used || (on_null && st == nullptr)) return true;
+  if (on_null) {
+    if (capturing(nullptr)) return false;
+    if (hipEventRecord(last_use, nullptr) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    on_null = false;
+  }
+  if (hipStreamWaitEvent(st, last_use, 0) == hipSuccess) return true;
+  (void)hipGetLastError();
+  return false;
+}
+hipError_t HipMem::leave(hipStream_t st) {
+  used = true;
+  on_null = st == nullptr;
+  return on_null ? hipSuccess : hipEventRecord(last_use, st);
+}
+
 bool HipMem::alloc(void **p, size_t bytes) {
   if (hipMalloc(p, bytes) == hipSuccess) return true;
   (void)hipGetLastError();
   return false;
 }
 void HipMem::free(void *p) {
-  if (used) (void)hipEventSynchronize(last_use);
+  if (used) (void)(on_null ? hipStreamSynchronize(nullptr) : hipEventSynchronize(last_use));
   (void)hipFree(p);
 }
 size_t HipMem::available() {
@@ -69,26 +97,18 @@ sap_status ensure_workspace(sap_ctx *ctx, size_t bytes, hipStream_t stream) {
   return SAP_OK;
 }
 
-static bool capturing(hipStream_t st) {
-  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
-  (void)hipGetLastError();  // the null stream beside another stream's capture
-  return true;
-}
-
 sap_status launch_apply_optional(sap_ctx *ctx, const sps_sketch *S, const void *A, int64_t lda, sap_dtype a_type,
                                  const double *b, int n, void *Y, int64_t ldy, sap_dtype y_type, void *work,
                                  size_t work_bytes, hipStream_t st, ApplyForm form) {
   const size_t wanted =
       apply_workspace_wanted(ctx, S->m, S->zeta, S->d, n, lda, b != nullptr, a_type, y_type, form);
   HipMem &mem = ctx->apply_mem;
-  if (wanted <= work_bytes || capturing(st) || !ctx->apply_opt.reserve(mem, wanted, ctx->budget - ctx->ws_size))
+  if (wanted <= work_bytes || capturing(st) || !ctx->apply_opt.reserve(mem, wanted, ctx->budget - ctx->ws_size) ||
+      !mem.enter(st))
     return launch_apply(ctx, S, A, lda, a_type, b, n, Y, ldy, y_type, work, work_bytes, st, form);
-  if (mem.used) SAP_HIP_TRY(hipStreamWaitEvent(st, mem.last_use, 0));
   const sap_status s = launch_apply(ctx, S, A, lda, a_type, b, n, Y, ldy, y_type, ctx->apply_opt.base,
                                     ctx->apply_opt.size, st, form);
-  mem.used = true;
-  SAP_HIP_TRY(hipEventRecord(mem.last_use, st));
+  SAP_HIP_TRY(mem.leave(st));
   return s;
 }
 

@@ -197,9 +197,14 @@ struct Server;
 
 struct HipMem {
   // The optional scratch's last use: calls on different streams share the buffer,
-  // so each one's stream waits for the one before it.
+  // so each one's stream waits for the one before it (enter, leave).  Its event is
+  // recorded as the call leaves, since a stream may be gone when the next one
+  // comes; on the null stream, which stays, only once another stream asks for it
+  // (the record costs a call 1 us among others, 3 alone).
   hipEvent_t last_use = nullptr;
-  bool used = false;
+  bool used = false, on_null = false;
+  bool enter(hipStream_t st);
+  hipError_t leave(hipStream_t st);
   bool alloc(void **p, size_t bytes);
   void free(void *p);
   size_t available();

@@ -56,20 +56,21 @@ def _exact_case(sap, m, n, d, adt, seed):
 
 
 def test_streams_share_scratch(sap):  # noqa: F811
-    """Asynchronous applies on two streams of one context, with lists, slices and
+    """Asynchronous applies on three streams of one context, the null stream among them, with lists, slices and
     packed rows of their own sizes."""
     import torch
     ctx = sap.Context(0)
     cases = [_exact_case(sap, 131072, 1024, 4000, torch.float32, 1), _exact_case(sap, 131072, 1024, 4001, torch.float32, 2),
              _exact_case(sap, 90001, 1030, 2400, torch.float32, 3)]
     print("scratch-streams", flush=True)
-    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    streams = [torch.cuda.Stream(), torch.cuda.default_stream(), torch.cuda.Stream()]
     outs = []
     for rep in range(6):
         for k, (A, idx, sign, d, ref) in enumerate(cases):
             Y = torch.full_like(ref, float("nan"))
-            streams[(rep + k) % 2].wait_stream(torch.cuda.current_stream())
-            with torch.cuda.stream(streams[(rep + k) % 2]):
+            st = streams[(rep * 2 + k + k // 2) % 3]
+            st.wait_stream(torch.cuda.current_stream())
+            with torch.cuda.stream(st):
                 sap.sps_apply(idx, sign, d, 8, A, None, ctx=ctx, Y=Y, y_dtype=torch.float64)
             outs.append((Y, ref))
     torch.cuda.synchronize()
