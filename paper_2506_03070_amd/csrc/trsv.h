@@ -173,6 +173,8 @@ __device__ __forceinline__ void trsv_invert_diag_block(const double *__restrict_
     double x[Q];
 #pragma unroll
     for (int rr = Q - 1; rr >= 0; --rr) {
+      x[rr] = 0.0;
+      if (o + rr >= kn) continue;  // uniform: nothing for an R of few rows to wait for
       double s = rr == c ? 1.0 : 0.0;
 #pragma unroll
       for (int k = rr + 1; k < Q; ++k) s -= sh.Rb[o + rr][o + k] * x[k];
