@@ -556,8 +556,9 @@ double scatter_us(int num_cus, int zeta, const ApplyPlan &p, bool pack, bool nea
                      p.nranges;
   const double items = static_cast<double>(p.nstrips) * p.nranges * p.nslices;
   const double rounds = std::ceil(items / num_cus);
-  // whole batches of rows of the 16 waves, a short last one as long as the others
-  const int64_t step = static_cast<int64_t>(kApplyWaves) * (kWave / p.w) * kUnroll;
+  // with zeta = 8 whole batches of rows of the 16 waves, a short last one as long
+  // as the others; the general path stops at the slice's last row
+  const int64_t step = zeta == 8 && p.nranges == 1 ? static_cast<int64_t>(kApplyWaves) * (kWave / p.w) * kUnroll : 1;
   const double rows = static_cast<double>((p.rows_per_slice + step - 1) / step * step);
   const double strip = (rows * zeta * p.w / 64.0) * clk / 2400.0 / p.nranges;
   return rounds * (strip + 5.0);  // 5: the strip cleared and written out
