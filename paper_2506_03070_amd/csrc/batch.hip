@@ -174,7 +174,7 @@ __device__ __forceinline__ void batch_apply_strip(const BatchItem &it, int strip
   const gmem<int32_t> *__restrict__ idx = gview(it.idx);
   for (int e = threadIdx.x; e < (d + 1) * kTileColsB; e += kBThreads) acc[e] = TY(0);
   __syncthreads();
-  // One row of [A b] per group of 16 lanes: its 16-column piece is loaded
+  // One row of [A b] per group of W lanes: its W-column piece is loaded
   // once and added into the zeta target rows; all loads of a batch of rows
   // are issued before the adds.
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
@@ -1053,9 +1053,9 @@ sap_status setup_items(sap_ctx *ctx, BatchItem *ditems, const std::vector<BatchI
   SAP_HIP_TRY(hipGetLastError());
   const int sh = (d_max + kPanelThreads - 1) / kPanelThreads;
   const int cols = n_max + 1;
-  // 4-column steps: twice the launches of 8-column ones, each with half the
-  // panel's dependent column reductions on the critical path (served
-  // stream p50 7.2 -> 6.5 ms, 512-problem batch 194 -> 189 ms)
+  // 4-column steps (against 8-column ones, measured when a panel still took a
+  // reduction per column: served stream p50 7.2 -> 6.5 ms, 512-problem batch 194 ->
+  // 189 ms; with panels from their Gram matrix only 4 columns have been measured)
   if (sh <= 1) launch_batch_qr<1, 4>(ditems, count, cols, st);
   else if (sh <= 2) launch_batch_qr<2, 4>(ditems, count, cols, st);
   else if (sh <= 4) launch_batch_qr<4, 4>(ditems, count, cols, st);

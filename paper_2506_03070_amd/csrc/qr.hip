@@ -507,8 +507,9 @@ sap_status qr_unblocked(sap_ctx *ctx, double *Y, int64_t ldy, int rows, int cols
   // VGPRs a lane keeps at 512 threads.  (1024 threads with S halved measured
   // ~20% slower at 4000 x 1001: the panels are bound by barriers and
   // cross-wave sums, which more waves lengthen.)  4-column blocks up to 2048
-  // rows as well: 8-column panels measured 20-25% slower there, twice the
-  // dependent column reductions per panel.
+  // rows as well: 8-column panels measured 20-25% slower there when a panel took
+  // a reduction per column; with panels from their Gram matrix, which take one,
+  // they have not been measured.
   if (rows <= 512) return qr_chain<1, 4>(ctx, Y, ldy, rows, cols, tau, work, st);
   if (rows <= 1024) return qr_chain<2, 4>(ctx, Y, ldy, rows, cols, tau, work, st);
   if (rows <= 2048) return qr_chain<4, 4>(ctx, Y, ldy, rows, cols, tau, work, st);

@@ -196,8 +196,7 @@ __device__ __forceinline__ void unit_lower(double (&V)[S][NB], int row0) {
 // J is a template parameter so that every register index of the panel P is
 // static (no scratch).
 template <int S, int NB, int J, int TH>
-__device__ __forceinline__ void panel_column(double (&P)[S][NB], PanelShared<NB, TH> &sh, int nb, int dr, int roff,
-                                             int k0, double *__restrict__ tau) {
+__device__ __forceinline__ void panel_column(double (&P)[S][NB], PanelShared<NB, TH> &sh, int nb, int dr, int roff) {
   constexpr int B = J & 1;  // LDS buffers alternate between columns: one barrier fewer
   const int t = threadIdx.x;
   const int lane = t & (kWave - 1), wave = t / kWave;
@@ -213,9 +212,8 @@ __device__ __forceinline__ void panel_column(double (&P)[S][NB], PanelShared<NB,
 #pragma unroll
     for (int x = 0; x < NB; ++x) acc[x] += a * P[s][x];
   }
-  // row J of the panel is held by one thread: in its register row 0 whenever
-  // J + roff < TH (every caller: roff <= NB), else found by selects with
-  // static indices only
+  // row J of the panel is held by one thread: in its register row 0 where
+  // J + roff < TH, else found by selects with static indices only
   if (J + roff < TH) {  // uniform
     if (J < dr && t == J + roff) {
 #pragma unroll
@@ -303,12 +301,11 @@ __device__ __forceinline__ void panel_column(double (&P)[S][NB], PanelShared<NB,
 }
 
 template <int S, int NB, int J, int TH>
-__device__ __forceinline__ void panel_columns(double (&P)[S][NB], PanelShared<NB, TH> &sh, int nb, int dr, int roff,
-                                              int k0, double *__restrict__ tau) {
+__device__ __forceinline__ void panel_columns(double (&P)[S][NB], PanelShared<NB, TH> &sh, int nb, int dr, int roff) {
   if constexpr (J < NB) {
     if (J < nb) {  // nb is uniform: every thread reaches the same barriers
-      panel_column<S, NB, J, TH>(P, sh, nb, dr, roff, k0, tau);
-      panel_columns<S, NB, J + 1, TH>(P, sh, nb, dr, roff, k0, tau);
+      panel_column<S, NB, J, TH>(P, sh, nb, dr, roff);
+      panel_columns<S, NB, J + 1, TH>(P, sh, nb, dr, roff);
     }
   }
 }
@@ -317,11 +314,11 @@ __device__ __forceinline__ void panel_columns(double (&P)[S][NB], PanelShared<NB
 // panel.  Ends without a barrier.
 template <int S, int NB, int TH>
 __device__ __forceinline__ void factor_panel_columns(double (&P)[S][NB], PanelShared<NB, TH> &sh, int nb, int dr,
-                                                     int roff, int k0, double *__restrict__ tau) {
+                                                     int roff) {
   const int t = threadIdx.x;
   if (t < NB * NB) sh.G[t / NB][t % NB] = 0.0;
   if (t < NB) sh.tauv[t] = 0.0;
-  panel_columns<S, NB, 0, TH>(P, sh, nb, dr, roff, k0, tau);  // its first barrier orders the zeroing
+  panel_columns<S, NB, 0, TH>(P, sh, nb, dr, roff);  // its first barrier orders the zeroing
   __syncthreads();
   if (t < NB) {
     const int l = t;
@@ -790,7 +787,7 @@ __device__ __forceinline__ void factor_update(double (&C)[S][NB], const double (
   }
   if (last && !gram) {
     __syncthreads();  // earlier users of the shared buffers are done
-    factor_panel_columns<S, NB, TH>(C, sh, nb, hi - roff, roff, k0, tau);
+    factor_panel_columns<S, NB, TH>(C, sh, nb, hi - roff, roff);
   } else if (last) {
     for_rows<S, NB, TH>(roff, [&](int s, int lr) {
 #pragma unroll
@@ -804,7 +801,7 @@ __device__ __forceinline__ void factor_update(double (&C)[S][NB], const double (
 template <int S, int NB, int TH, typename StoreT>
 __device__ __forceinline__ void factor_first_short(double (&C)[S][NB], PanelShared<NB, TH> &sh, int nb, int rows,
                                                    double *__restrict__ tau, StoreT &&store_t) {
-  factor_panel_columns<S, NB, TH>(C, sh, nb, rows, 0, 0, tau);
+  factor_panel_columns<S, NB, TH>(C, sh, nb, rows, 0);
   publish_small<NB, TH>(sh, nb, 0, tau, store_t);
 }
 
