@@ -425,10 +425,9 @@ __device__ __forceinline__ double reciprocal(double a) {
 // (see the accuracy note at factor_update), and at least kGramTiny of it in
 // absolute terms (the root's estimate is for normal numbers; an exactly zero
 // column is taken).  A norm whose square overflows is refused too.
-constexpr double kGramKeep = 0.9;
-// With fewer rows the rows that the update turns into R's take more than that:
-// such panels are factored column by column without asking (10 x 2: 25 -> 21 us,
-// 64 x 33: 87 -> 72).
+constexpr double kGramKeep = 0.75;
+// With fewer rows the ones that the update turns into R's take up to that much:
+// such panels are factored column by column without asking (10 x 2: 25 -> 21 us).
 constexpr int kGramRows = 64;
 constexpr double kGramTiny = 1e-280;
 constexpr double kGramHuge = 1e307;
@@ -716,14 +715,16 @@ __device__ __forceinline__ void publish_small(PanelShared<NB, TH> &sh, int nb, i
 // Accuracy.  Each norm and product below the diagonal comes from G by
 // subtraction; what a norm is off by, all rows of its reflector share.  The
 // subtrahends are therefore summed by themselves, G's last sum keeps its
-// rounding errors, and a column whose norm falls below nine tenths of the one
-// that G was summed for (correlated columns, fewer than about 80 rows, nothing
-// below the diagonal, non-finite entries) has its panel factored column by
-// column.  Against an 80-bit factorisation, over that of the column-by-column form
-// throughout (R and V; max ||(Q R - Y)_j|| / ||Y_j||; ||Q^T Q - I||; 400 x 101
-// columns of norms 1 to 1e-4): 0.89, 1.00, 0.96; with G rounded at every step and a
-// share of a quarter 1.31, 1.12, 1.36, and on correlated columns (singular values
-// 1 to 1e-6) 1.1, 1.6, 1.4 against 1.00.
+// rounding errors, and a panel with a column whose norm falls below three quarters
+// of the one that G was summed for (correlated columns, fewer than about 40 rows,
+// nothing below the diagonal, non-finite entries) is factored column by column.
+// Against an 80-bit factorisation, over the error of the column-by-column form
+// throughout (R and V; max ||(Q R - Y)_j|| / ||Y_j||; ||Q^T Q - I||): 0.85, 0.98, 0.95
+// for 400 x 101 columns of norms 1 to 1e-4, and 0.97, 0.93, 0.93 for 800 x 201 with
+// singular values that fall by six decades in 1000; with G rounded at every step
+// and a share of a quarter 1.31, 1.12, 1.36 for the first.  At 0.65 the short and
+// correlated panels come out up to 1.04; at 0.9 most panels of the second
+// kind would go column by column (4000 x 1001: 3.9 ms instead of 2.1).
 //
 // warm: the panel has kGramRows rows, and gram_prepare and gram_total ran (without:
 // the update alone, or with last the column-by-column form).  warm without last
