@@ -26,8 +26,8 @@
 // workgroup reduction per column and selects on every row: apply 6.7, factor
 // 6.5.  4000 x 1001: 3.96 -> 2.10 ms, 2000 x 501: 1.50 -> 0.78, 1026 x 257: 0.75 ->
 // 0.40, 400 x 101: 0.245 -> 0.130, 8000 x 1001: 6.67 -> 4.98, 64 x 33 (mostly column
-// by column): 0.090 -> 0.073; with correlated columns (singular values 1 to 1e-6),
-// where some panels go column by column, 4000 x 1001: 3.95 -> 2.34.  1 to 6% of that
+// by column): 0.089 -> 0.073; with correlated columns (singular values 1 to 1e-8),
+// where some panels go column by column, 4000 x 1001: 3.96 -> 2.26.  1 to 6% of that
 // goes into the Gram form's exactness (factor_update in qr_dev.h): 2.05, 0.75, 0.38,
 // 0.124, 4.91 without.
 // Sketches taller than 4096 rows and wider than 192 columns take the

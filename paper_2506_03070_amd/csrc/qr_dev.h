@@ -425,7 +425,8 @@ __device__ __forceinline__ double reciprocal(double a) {
 // (see the accuracy note at factor_update), and at least kGramTiny of it in
 // absolute terms (the root's estimate is for normal numbers; an exactly zero
 // column is taken).  A norm whose square overflows is refused too.
-constexpr double kGramKeep = 0.75;
+constexpr double kGramKeep = 0.75, kGramKeepTall = 0.65;
+constexpr int kGramTall = 256;  // rows from which it is the smaller
 // With fewer rows the ones that the update turns into R's take up to that much:
 // such panels are factored column by column without asking (10 x 2: 25 -> 21 us).
 constexpr int kGramRows = 64;
@@ -520,7 +521,7 @@ struct PackedPairs {
 // factor_update).  w2 as wy_product returns it.  Fills sh.top, sh.U, sh.tauv,
 // sh.T and sh.slow; the caller's barrier follows the first three.
 template <int NB, int TH>
-__device__ __forceinline__ void factor_small(PanelShared<NB, TH> &sh, int nb, double w2, bool last) {
+__device__ __forceinline__ void factor_small(PanelShared<NB, TH> &sh, int nb, double w2, double share, bool last) {
   constexpr int NG = PanelShared<NB, TH>::kGram;
   int lane = threadIdx.x & (kWave - 1);
   asm volatile("" : "+v"(lane));  // its LDS addresses are formed here, not kept through the chain's loop
@@ -594,7 +595,7 @@ __device__ __forceinline__ void factor_small(PanelShared<NB, TH> &sh, int nb, do
       const double alpha = a[J][J], sq = tot[J];
       const bool zero = keep[J] == 0.0;
       // (NaN: refused)
-      bad = bad || !(zero || (sq >= kGramKeep * keep[J] && sq >= kGramTiny && keep[J] <= kGramHuge));
+      bad = bad || !(zero || (sq >= share * keep[J] && sq >= kGramTiny && keep[J] <= kGramHuge));
       double beta = alpha, scale = 0.0;
       if (!zero) {
         double nrm, inv;
@@ -715,16 +716,17 @@ __device__ __forceinline__ void publish_small(PanelShared<NB, TH> &sh, int nb, i
 // Accuracy.  Each norm and product below the diagonal comes from G by
 // subtraction; what a norm is off by, all rows of its reflector share.  The
 // subtrahends are therefore summed by themselves, G's last sum keeps its
-// rounding errors, and a panel with a column whose norm falls below three quarters
-// of the one that G was summed for (correlated columns, fewer than about 40 rows,
-// nothing below the diagonal, non-finite entries) is factored column by column.
+// rounding errors, and a panel with a column whose norm falls below 0.65 (0.75 with
+// fewer than 256 rows) of the one that G was summed for (correlated columns, few
+// rows, nothing below the diagonal, non-finite entries) is factored column by column.
 // Against an 80-bit factorisation, over the error of the column-by-column form
 // throughout (R and V; max ||(Q R - Y)_j|| / ||Y_j||; ||Q^T Q - I||): 0.85, 0.98, 0.95
-// for 400 x 101 columns of norms 1 to 1e-4, and 0.97, 0.93, 0.93 for 800 x 201 with
-// singular values that fall by six decades in 1000; with G rounded at every step
-// and a share of a quarter 1.31, 1.12, 1.36 for the first.  At 0.65 the short and
-// correlated panels come out up to 1.04; at 0.9 most panels of the second
-// kind would go column by column (4000 x 1001: 3.9 ms instead of 2.1).
+// for 400 x 101 columns of norms 1 to 1e-4, and 0.97, 0.94, 0.94 for 800 x 201 with
+// singular values that fall by eight decades in 1000; with G rounded at every step
+// and a share of a quarter 1.31, 1.12, 1.36 for the first.  Where the shares
+// lie: at 0.65 panels of 70 to 130 rows come out at up to 1.04, at 0.5 taller ones at
+// 1.02 to 1.04; at 0.75 91 of the 251 panels of a 4000 x 1001 sketch of the
+// second kind go column by column (2.9 ms), at 0.65 21 (2.26).
 //
 // warm: the panel has kGramRows rows, and gram_prepare and gram_total ran (without:
 // the update alone, or with last the column-by-column form).  warm without last
@@ -750,7 +752,7 @@ __device__ __forceinline__ void factor_update(double (&C)[S][NB], const double (
   __builtin_amdgcn_sched_barrier(0);
   if (warm) {
     if (wave == 0)
-      factor_small<NB, TH>(sh, nb, w2, last);
+      factor_small<NB, TH>(sh, nb, w2, hi - roff >= kGramTall ? kGramKeepTall : kGramKeep, last);
     else
       __syncthreads();
   }
