@@ -363,10 +363,10 @@ struct Piece {
 // return in order, so a list asked for behind a whole tile would wait for all
 // of it (that cost 1.65 ms of 4.3 at 2^20 x 1000, d = 4000).  Lists run three
 // chunks ahead.  Bound by the lines that move from L2: a row's 16- or 32-byte
-// piece takes a 128-byte line (2^19 x 1000 FP64: 1.3e8 requests, 17 GB; 1.77 ms,
-// 1.18 without the tile loads).  The LDS reads (8.5 cycles a 16-byte wave read,
-// half of them bank conflicts) and the vector work (10 instructions an entry of 4
-// columns) come next; lists are about twice as long as their entries, since the
+// piece takes a 128-byte line (2^19 x 1000 FP64: 1.3e8 of the 1.7e8 requests, 17 of 22
+// GB, 1.67 ms; 1.18 of then 1.76 without the tile loads).  The LDS
+// (active 73% of the kernel, 10 cycles an instruction, 59% of them bank conflicts) and
+// the vector work (10 instructions an entry of 4 columns) come next; lists are about twice as long as their entries, since the
 // 64 rows of a group wait for the longest.
 template <typename TA, typename TO, int S, int W>
 __global__ __launch_bounds__(kApplyThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void apply_gather_kernel(

@@ -19,9 +19,9 @@
 // before it, so the chain completes whatever number of them is resident.
 //
 // What bounds it: the dependent chain from panel to panel (not the flops: 4%
-// of the FP64 peak at 4000 x 1001).  Per 4-column panel at 4000 rows 8.2 us:
-// V^T C 1.5, W2 0.4, the panel's 4 reflectors 1.6, update and new rows 0.8, the
-// rest the rows' way out of one CU and into the next (128 KB; 4.5 us when the
+// of the FP64 peak at 4000 x 1001).  Per 4-column panel at 4000 rows 8.4 us,
+// 0.2 of them the Gram form's exactness: V^T C 1.5, W2 0.4, the panel's 4 reflectors
+// 1.6, update and new rows 0.8, the rest the rows' way out of one CU and into the next (128 KB; 4.5 us when the
 // next block waited for the flag, see kDirect below).  16.0 us with one
 // workgroup reduction per column and selects on every row: apply 6.7, factor
 // 6.5.  4000 x 1001: 3.96 -> 2.10 ms, 2000 x 501: 1.50 -> 0.78, 1026 x 257: 0.75 ->
